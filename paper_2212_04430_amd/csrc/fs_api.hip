@@ -909,7 +909,7 @@ struct BatchSolver {
     long long dslash_calls = 0;
     size_t part_doubles = 0;
     // doubles of partial sums the launches over plan q may write
-    size_t part_need(const Plan& q) const { return (size_t)q.max_wg() * 32 * q.nr; }
+    size_t part_need(const Plan& q) const { return (size_t)q.max_wg() * 8 * q.nr; }
 
     BatchSolver(Plan& plan, const std::vector<fs_ctx_s*>& l, hipStream_t stream, const SolveOpts& opts)
         : full(plan), eo_pl(opts.eo ? eo_plan_of(plan, l, stream, opts.P, opts.eo_var, opts.eo_occ) : nullptr),
@@ -936,8 +936,7 @@ struct BatchSolver {
         d_rc.alloc(sizeof(uint32_t) * (size_t)S);
         d_diag.alloc(sizeof(double) * pl.nsys);
         d_st.alloc(sizeof(SysState) * pl.nsys);
-        // partial sums: at most 8 doubles per rhs per workgroup (32 for the hop
-        // launches of the bilinears, which callers run over the full-lattice plan)
+        // partial sums: at most 8 doubles per rhs per workgroup
         part_doubles = std::max(part_need(pl), part_need(full));
         d_part.alloc(sizeof(double) * part_doubles);
         d_flags.alloc(sizeof(int) * 2 * pl.blocks.size());
@@ -1286,6 +1285,21 @@ DevBuf to_device(const void* src, size_t n, int is_device, hipStream_t s) {
     return d;
 }
 
+// A user buffer of n bytes as 16-byte aligned device memory: the buffer itself
+// where it is that (said by is_device, or by the runtime: the binding passes
+// device tensors to calls whose outputs are host arrays), else a copy in `stage`.
+const double* device_view(const double* p, size_t n, int is_device, int device, DevBuf& stage, hipStream_t s) {
+    bool dev = is_device != 0;
+    if (!dev) {
+        hipPointerAttribute_t a;
+        dev = hipPointerGetAttributes(&a, p) == hipSuccess && a.type == hipMemoryTypeDevice && a.device == device;
+        (void)hipGetLastError();  // plain host memory is not an error here
+    }
+    if (dev && (reinterpret_cast<uintptr_t>(p) & 15) == 0) return p;
+    stage = to_device(p, n, is_device, s);
+    return stage.as<double>();
+}
+
 void from_device(void* dst, const DevBuf& d, size_t n, int is_device, hipStream_t s) {
     HC(hipMemcpyAsync(dst, d.p, n, is_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s));
     HC(hipStreamSynchronize(s));
@@ -1359,6 +1373,56 @@ void build_clover(fs_ctx_s* c) {
     std::memcpy(&nrm, &bits, sizeof(nrm));
     if (!std::isfinite(nrm)) fail(FS_E_ARG, "the clover term is not finite (links not finite?)");
     c->clv_norm = nrm;
+}
+
+// Spin correlations of the blocks with on[b] set: d_M[(sys * P1 + p) * 32 + k] of
+// x and Omega_p, y the partner block yb[2 b] of yfld (or, at -1, the block's own
+// spinor of src).  One pass over the fields where the fused kernel applies, else
+// one launch per p with the displaced field in phi and a second field.
+void bilinear_pass(const Plan& pl, const std::vector<fs_ctx_s*>& lats, const std::vector<char>& on,
+                   const std::vector<int>& yb, int P1, Fld x, Fld yfld, Fld src, Fld phi, double* d_M, hipStream_t s) {
+    const int nblk = (int)pl.blocks.size();
+    int max_lz = 0;
+    for (const fs_ctx_s* c : lats) max_lz = std::max(max_lz, c->dims[2]);
+    const int rs = bilin_rs(pl.nr, max_lz, P1);
+    std::vector<int> start(nblk + 1, 0);
+    int gpw = 1;
+    if (rs) {
+        // about 2048 workgroups: two fit a CU (LDS, registers), four rounds even out their ends
+        long long groups = 0;
+        for (int b = 0; b < nblk; ++b)
+            if (on[b]) groups += bilin_groups_of(lats[pl.blocks[b].lat]->dims, rs) * (pl.nr / rs);
+        gpw = (int)std::max<long long>(1, groups / 2048);
+    }
+    for (int b = 0; b < nblk; ++b) {
+        int n = 0;
+        if (on[b] && rs)
+            n = (int)((bilin_groups_of(lats[pl.blocks[b].lat]->dims, rs) + gpw - 1) / gpw) * (pl.nr / rs);
+        else if (on[b])
+            n = pl.wg_start[b + 1] - pl.wg_start[b];
+        start[b + 1] = start[b] + n;
+    }
+    DevBuf d_start = to_device(start.data(), sizeof(int) * (nblk + 1), 0, s);
+    DevBuf d_yb = to_device(yb.data(), sizeof(int) * 2 * nblk, 0, s);
+    Work w = pl.work(P64, false);
+    w.wg_start = d_start.as<int>();
+    w.total_wg = start.back();
+    DevBuf part(sizeof(double) * 32 * (size_t)w.total_wg * (rs ? (size_t)P1 * rs : (size_t)pl.nr));
+    Field phi1;
+    if (rs) {
+        launch_bilinears(w, rs, gpw, P1, x, yfld, src, d_yb.as<int>(), part.as<double>(), d_M, s);
+    } else {
+        phi1.alloc(P64, pl.total_slots);
+        Fld cur = x;
+        for (int p = 0; p < P1; ++p) {
+            Fld out = (p % 2 == 1) ? phi : phi1.f();
+            launch_hop_reduce(w, p, out, cur, yfld, src, d_yb.as<int>(), part.as<double>(), s);
+            launch_hop_finish(w, part.as<double>(), d_M, P1, p, s);
+            if (p > 0) cur = out;
+        }
+    }
+    HC(hipGetLastError());
+    HC(hipStreamSynchronize(s));  // the tables and fields die with this scope
 }
 
 // One batched pass over a set of (instance, level, sample) units.  For each
@@ -1445,11 +1509,9 @@ void run_units(const std::vector<fs_ctx_s*>& ctxs, const fs_est_params* prm, con
     if (want_bound) {
         std::vector<int> ys(2 * nblk, 0);
         for (int b2 = 0; b2 < nblk; ++b2) ys[2 * b2] = b2;
-        DevBuf d_ys = to_device(ys.data(), sizeof(int) * 2 * nblk, 0, s);
-        const Work wn = pl->work(P64, false);
         DevBuf d_N(sizeof(double) * (size_t)nsys * 32);
-        launch_hop_reduce(wn, 0, Fld(), bs.xhi.f(), bs.xhi.f(), Fld(), d_ys.as<int>(), bs.part(), s);
-        launch_hop_finish(wn, bs.part(), d_N.as<double>(), 1, 0, s);
+        bilinear_pass(*pl, ctxs, std::vector<char>(nblk, 1), ys, 1, bs.xhi.f(), bs.xhi.f(), Fld(), Fld(),
+                      d_N.as<double>(), s);
         std::vector<double> hN((size_t)nsys * 32);
         HC(hipMemcpyAsync(hN.data(), d_N.p, sizeof(double) * hN.size(), hipMemcpyDeviceToHost, s));
         HC(hipStreamSynchronize(s));
@@ -1482,32 +1544,16 @@ void run_units(const std::vector<fs_ctx_s*>& ctxs, const fs_est_params* prm, con
             }
     }
 
-    // bilinears: hop launches over x-blocks only (y-blocks get no workgroups)
-    std::vector<int> yb(2 * nblk, -1), hop_start(nblk + 1, 0);
+    // bilinears over the x-blocks (y-blocks get no workgroups)
+    std::vector<int> yb(2 * nblk, -1);
     std::vector<char> is_x(nblk, 0);
     for (auto& pr : pairs) {
         is_x[pr.first] = 1;
         yb[2 * pr.first] = pr.second;
         yb[2 * pr.first + 1] = pr.second >= 0 ? 1 : 0;
     }
-    for (int b = 0; b < nblk; ++b)
-        hop_start[b + 1] = hop_start[b] + (is_x[b] ? pl->wg_start[b + 1] - pl->wg_start[b] : 0);
-    DevBuf d_hop_start = to_device(hop_start.data(), sizeof(int) * (nblk + 1), 0, s);
-    DevBuf d_yb = to_device(yb.data(), sizeof(int) * 2 * nblk, 0, s);
-    Work wh = pl->work(P64, false);
-    wh.wg_start = d_hop_start.as<int>();
-    wh.total_wg = hop_start.back();
     DevBuf d_M(sizeof(double) * (size_t)nsys * P1 * 32);
-    Field phi1;
-    phi1.alloc(P64, pl->total_slots);
-    // ping-pong: p=0 reads xhi; then phi in rhi / phi1
-    Fld cur = bs.xhi.f();
-    for (int p = 0; p <= prm->p_max; ++p) {
-        Fld out = (p % 2 == 1) ? bs.rhi.f() : phi1.f();
-        launch_hop_reduce(wh, p, out, cur, bs.xhi.f(), bs.b.f(), d_yb.as<int>(), bs.part(), s);
-        launch_hop_finish(wh, bs.part(), d_M.as<double>(), P1, p, s);
-        if (p > 0) cur = out;
-    }
+    bilinear_pass(*pl, ctxs, is_x, yb, P1, bs.xhi.f(), bs.xhi.f(), bs.b.f(), bs.rhi.f(), d_M.as<double>(), s);
     // contraction into the per-sample estimates
     std::vector<XMap> xm(nsys);
     for (int i = 0; i < nsys; ++i) {
@@ -1673,35 +1719,20 @@ void probed_impl(fs_ctx_s* c, const fs_est_params* prm, const double* sigma_in, 
 
     // bilinears: x-blocks only, paired with the y-block of the same sources (or their own source on level L)
     static const GammaTab gt = make_gamma_tab();
-    std::vector<int> yb(2 * nblk, -1), hop_start(nblk + 1, 0);
+    std::vector<int> yb(2 * nblk, -1);
+    std::vector<char> is_x(nblk, 0);
     for (int l = 0; l <= L; ++l)
         for (int b = 0; b < nbg; ++b) {
             const int xb = gx[l] * nbg + b;
+            is_x[xb] = 1;
             if (l < L) {
                 yb[2 * xb] = gy[l] * nbg + b;
                 yb[2 * xb + 1] = 1;
             }
         }
-    std::vector<char> is_x_group(ngroups, 0);
-    for (int l = 0; l <= L; ++l) is_x_group[gx[l]] = 1;
-    for (int b = 0; b < nblk; ++b)
-        hop_start[b + 1] = hop_start[b] + (is_x_group[b / nbg] ? pl->wg_start[b + 1] - pl->wg_start[b] : 0);
-    DevBuf d_hop_start = to_device(hop_start.data(), sizeof(int) * (nblk + 1), 0, s);
-    DevBuf d_yb = to_device(yb.data(), sizeof(int) * 2 * nblk, 0, s);
     DevBuf d_xm = to_device(xm.data(), sizeof(XMap) * nsys, 0, s);
-    Work wh = pl->work(P64, false);
-    wh.wg_start = d_hop_start.as<int>();
-    wh.total_wg = hop_start.back();
     DevBuf d_M(sizeof(double) * (size_t)nsys * P1 * 32);
-    Field phi1;
-    phi1.alloc(P64, pl->total_slots);
-    Fld cur = bs.xhi.f();
-    for (int p = 0; p <= prm->p_max; ++p) {
-        Fld outf = (p % 2 == 1) ? bs.rhi.f() : phi1.f();
-        launch_hop_reduce(wh, p, outf, cur, bs.xhi.f(), bs.b.f(), d_yb.as<int>(), bs.part(), s);
-        launch_hop_finish(wh, bs.part(), d_M.as<double>(), P1, p, s);
-        if (p > 0) cur = outf;
-    }
+    bilinear_pass(*pl, lats, is_x, yb, P1, bs.xhi.f(), bs.xhi.f(), bs.b.f(), bs.rhi.f(), d_M.as<double>(), s);
     DevBuf d_Y(sizeof(double) * 2 * (size_t)nsys * 16 * P1);
     launch_gamma_contract(d_M.as<double>(), P1, nsys, d_xm.as<XMap>(), gt, d_Y.as<double>(), 1, s);
     std::vector<int> g0((size_t)(L + 1) * N);
@@ -1854,8 +1885,6 @@ void sampling_impl(fs_ctx_s* c, const fs_est_params* prm, const double* sh_in, i
     std::vector<double> X(xsz, 0.0);
     DevBuf d_X = to_device(X.data(), sizeof(double) * xsz, 0, s);
     DevBuf d_M(sizeof(double) * (size_t)nsys * P1 * 32);
-    Field phi1;
-    phi1.alloc(P64, pl->total_slots);
     // hopping parameter expansion of the singles: w = (H/a)^k x for the x-blocks
     // of shifts with m0 + s > 0 (x elsewhere), H = a - (D + s): k rounds of the
     // stencil with a zero diagonal (giving -H w) and a scale by -1/a
@@ -1865,6 +1894,8 @@ void sampling_impl(fs_ctx_s* c, const fs_est_params* prm, const double* sh_in, i
         for (int b = 0; b < nblk; b += 2)
             if (prm->hpe_order > 0 && prm->solve.m0 + sh[(b / 2) / nch] > 0.0) eb.push_back(pl->blocks[b]);
         if (!eb.empty()) {
+            Field phi1;
+            phi1.alloc(P64, pl->total_slots);
             whpe.alloc(P64, pl->total_slots);
             HC(hipMemcpyAsync(whpe.v.p, bs.xhi.v.p, whpe.v.n < bs.xhi.v.n ? whpe.v.n : bs.xhi.v.n,
                               hipMemcpyDeviceToDevice, s));
@@ -1916,7 +1947,8 @@ void sampling_impl(fs_ctx_s* c, const fs_est_params* prm, const double* sh_in, i
     }
     for (int q = 0; q <= m; ++q) {
         const int iy = q - 1;
-        std::vector<int> yb(2 * nblk, -1), hop_start(nblk + 1, 0);
+        std::vector<int> yb(2 * nblk, -1);
+        std::vector<char> on(nblk, 0);
         std::vector<XMap> xm(nsys);
         for (int b = 0; b < nblk; ++b) {
             const int j = (b / 2) / nch, ch = (b / 2) % nch;
@@ -1925,7 +1957,7 @@ void sampling_impl(fs_ctx_s* c, const fs_est_params* prm, const double* sh_in, i
                 yb[2 * b] = 2 * (iy * nch + ch) + 1;
                 yb[2 * b + 1] = 1;
             }
-            hop_start[b + 1] = hop_start[b] + (part_of ? pl->wg_start[b + 1] - pl->wg_start[b] : 0);
+            on[b] = part_of;
             for (int r = 0; r < nr; ++r) {
                 const int sys = b * nr + r;
                 XMap mp;
@@ -1937,19 +1969,9 @@ void sampling_impl(fs_ctx_s* c, const fs_est_params* prm, const double* sh_in, i
                 xm[sys] = mp;
             }
         }
-        DevBuf d_hop_start = to_device(hop_start.data(), sizeof(int) * (nblk + 1), 0, s);
-        DevBuf d_yb = to_device(yb.data(), sizeof(int) * 2 * nblk, 0, s);
         DevBuf d_xm = to_device(xm.data(), sizeof(XMap) * nsys, 0, s);
-        Work wh = pl->work(P64, false);
-        wh.wg_start = d_hop_start.as<int>();
-        wh.total_wg = hop_start.back();
-        Fld cur = (q == 0 && whpe.v.p) ? whpe.f() : bs.xhi.f();
-        for (int p = 0; p <= prm->p_max; ++p) {
-            Fld outf = (p % 2 == 1) ? bs.rhi.f() : phi1.f();
-            launch_hop_reduce(wh, p, outf, cur, bs.xhi.f(), bs.b.f(), d_yb.as<int>(), bs.part(), s);
-            launch_hop_finish(wh, bs.part(), d_M.as<double>(), P1, p, s);
-            if (p > 0) cur = outf;
-        }
+        bilinear_pass(*pl, lats, on, yb, P1, (q == 0 && whpe.v.p) ? whpe.f() : bs.xhi.f(), bs.xhi.f(), bs.b.f(),
+                      bs.rhi.f(), d_M.as<double>(), s);
         launch_gamma_contract(d_M.as<double>(), P1, nsys, d_xm.as<XMap>(), gt, d_X.as<double>(), N, s);
         HC(hipStreamSynchronize(s));  // the host tables above die with this scope
     }
@@ -2893,45 +2915,52 @@ fs_status fs_bilinear(fs_ctx c, int32_t p_max, const double* y, const double* x,
         DeviceScope ds(c->device);
         hipStream_t s = c->stream;
         const int P1 = p_max + 1;
+        static const GammaTab gt = make_gamma_tab();
+        const size_t nb = sizeof(double) * 24 * (size_t)c->V;
+        const size_t on = sizeof(double) * 32 * P1;
+        if (bilin_rs(1, c->dims[2], P1)) {
+            DevBuf bx, by;
+            const double* vx = device_view(x, nb, is_device, c->device, bx, s);
+            const double* vy = device_view(y, nb, is_device, c->device, by, s);
+            const long long groups = bilin_groups_of(c->dims, 1);
+            const int gpw = (int)std::max<long long>(1, groups / 2048);
+            const int nwg = (int)((groups + gpw - 1) / gpw);
+            DevBuf part(sizeof(double) * 32 * (size_t)P1 * nwg), d_o(on);
+            launch_bilin_canonical(lat_desc(c, P64), vx, vy, P1, gpw, nwg, part.as<double>(), gt, d_o.as<double>(), s);
+            HC(hipGetLastError());
+            if (is_device) {
+                HC(hipMemcpyAsync(out, d_o.p, on, hipMemcpyDeviceToDevice, s));
+                HC(hipStreamSynchronize(s));
+            } else {
+                c->pinned.ensure(on);
+                HC(hipMemcpyAsync(c->pinned.p, d_o.p, on, hipMemcpyDeviceToHost, s));
+                HC(hipStreamSynchronize(s));
+                std::memcpy(out, c->pinned.p, on);
+            }
+            return;
+        }
         std::vector<int> blk_lat{0, 0};  // block 0: x, block 1: y (no workgroups in hop launches)
         std::vector<fs_ctx_s*> lats{c};
         auto pl = make_plan(blk_lat, lats, 1, 256, s);
-        const size_t nb = sizeof(double) * 24 * (size_t)c->V;
         DevBuf dx = to_device(x, nb, is_device, s);
         DevBuf dy = to_device(y, nb, is_device, s);
-        Field fx, f1, f2;
+        Field fx, f1;
         fx.alloc(P64, pl->total_slots);
         f1.alloc(P64, pl->total_slots);
-        f2.alloc(P64, pl->total_slots);
         std::vector<int> map_x{0, -2}, map_y{-2, 0};
         DevBuf dmx = to_device(map_x.data(), sizeof(int) * 2, 0, s);
         DevBuf dmy = to_device(map_y.data(), sizeof(int) * 2, 0, s);
         launch_pack(P64, pl->work(P64, false), fx.f(), dx.as<double>(), 0, dmx.as<int>(), s);
         launch_pack(P64, pl->work(P64, false), fx.f(), dy.as<double>(), 0, dmy.as<int>(), s);
-        std::vector<int> hop_start{0, pl->wg_start[1], pl->wg_start[1]};
-        DevBuf d_hs = to_device(hop_start.data(), sizeof(int) * 3, 0, s);
-        std::vector<int> yb{1, 0, -1, 0};
-        DevBuf d_yb = to_device(yb.data(), sizeof(int) * 4, 0, s);
-        Work wh = pl->work(P64, false);
-        wh.wg_start = d_hs.as<int>();
-        wh.total_wg = hop_start.back();
-        DevBuf d_part(sizeof(double) * (size_t)pl->wg_start.back() * 32);
         DevBuf d_M(sizeof(double) * 2 * P1 * 32);
-        Fld cur = fx.f();
-        for (int p = 0; p <= p_max; ++p) {
-            Fld o = (p % 2 == 1) ? f1.f() : f2.f();
-            launch_hop_reduce(wh, p, o, cur, fx.f(), Fld(), d_yb.as<int>(), d_part.as<double>(), s);
-            launch_hop_finish(wh, d_part.as<double>(), d_M.as<double>(), P1, p, s);
-            if (p > 0) cur = o;
-        }
+        bilinear_pass(*pl, lats, {1, 0}, {1, 0, -1, 0}, P1, fx.f(), fx.f(), Fld(), f1.f(), d_M.as<double>(), s);
         std::vector<XMap> xm(2);
         std::memset(xm.data(), 0, sizeof(XMap) * 2);
         xm[0].level = 0;
         xm[0].coef = 1.0;
         xm[1].level = -1;
         DevBuf d_xm = to_device(xm.data(), sizeof(XMap) * 2, 0, s);
-        static const GammaTab gt = make_gamma_tab();
-        DevBuf d_X(sizeof(double) * 16 * P1 * 2);
+        DevBuf d_X(on);
         launch_gamma_contract(d_M.as<double>(), P1, 2, d_xm.as<XMap>(), gt, d_X.as<double>(), 1, s);
         HC(hipGetLastError());
         // X layout [n][p] -> out [p][n]

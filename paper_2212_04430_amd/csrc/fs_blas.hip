@@ -887,6 +887,281 @@ __global__ void __launch_bounds__(256) k_ms_update(Work w, int nm, Fld sf, Fld v
     FS_WG_EPILOGUE
 }
 
+// Adds row a of the contraction with Gamma_n, Gamma_n[a, c] M_ac with c = perm_n(a):
+// every Gamma_n of the DeGrand-Rossi basis has one nonzero (a power of i) per row.
+__device__ __forceinline__ void gamma_term(const GammaTab& gt, int n, int a, const double* __restrict__ M, double& re,
+                                           double& im) {
+    const int c = gt.perm[n][a];
+    const double mr = M[2 * (4 * a + c)], mi = M[2 * (4 * a + c) + 1];
+    const int ph = gt.ph[n][a];
+    const double gr = ph == 0 ? 1.0 : ph == 2 ? -1.0 : 0.0;
+    const double gi = ph == 1 ? 1.0 : ph == 3 ? -1.0 : 0.0;
+    re += gr * mr - gi * mi;
+    im += gr * mi + gi * mr;
+}
+
+// ------------------------------------------------------------------ fused displaced bilinears
+//
+// M_ab(p) = sum_{x,c} conj(y_a(x)) . phi_b(x), phi = Omega_p x, for every p =
+// 0..P1-1 in one pass over the fields.  Omega_p couples the sites of one z-line
+// only, so a workgroup that holds whole z-lines reads x, y and U_z once, keeps
+// them in registers and passes phi from the lane of z + 1 to that of z through
+// LDS (one 48 KiB buffer, two barriers per p), where the one-hop kernel below
+// reads y, phi and U_z and writes phi for every p.
+//
+// Lane (rr, column, z) of 256: RS of the block's nr systems, then the
+// consecutive (x, y, t) columns that fit, then z.  A workgroup walks gpw groups
+// of columns; the 32 sums of a p are formed per wave by halving (each exchange
+// sums two values at once and leaves half of them in each half of the lanes:
+// 32 exchanges for 32 values instead of 192) and added up in LDS.
+//
+// Bound: the FP64 multiply-adds (336 per site, system and p) and the reduction
+// against 3 x 192 + 144 bytes per site, system and p of the one-hop kernel.
+// Measured, p = 0..8 on 16^3x32: one pair of spinors 593 -> 51 us a call (all of
+// fs_bilinear), the 240 pairs of the 432-system estimate 31 -> 6 ms of its 624.
+
+// a and b summed over the pairs of lanes OFF apart: lanes with the OFF bit
+// clear receive a's sum, the others b's.
+template <int OFF>
+__device__ __forceinline__ double halve(double a, double b) {
+    if constexpr (OFF >= 16) {
+        uint32_t al = (uint32_t)__double2loint(a), ah = (uint32_t)__double2hiint(a);
+        uint32_t bl = (uint32_t)__double2loint(b), bh = (uint32_t)__double2hiint(b);
+        if constexpr (OFF == 32) {
+            const auto l = __builtin_amdgcn_permlane32_swap(al, bl, false, false);
+            const auto h = __builtin_amdgcn_permlane32_swap(ah, bh, false, false);
+            al = l[0]; bl = l[1]; ah = h[0]; bh = h[1];
+        } else {
+            const auto l = __builtin_amdgcn_permlane16_swap(al, bl, false, false);
+            const auto h = __builtin_amdgcn_permlane16_swap(ah, bh, false, false);
+            al = l[0]; bl = l[1]; ah = h[0]; bh = h[1];
+        }
+        return __hiloint2double((int)ah, (int)al) + __hiloint2double((int)bh, (int)bl);
+    } else {
+        const bool hi = threadIdx.x & OFF;
+        const double send = hi ? a : b, keep = hi ? b : a;
+        return keep + __shfl_xor(send, OFF, 64);
+    }
+}
+
+// The groups g0..g1-1 of columns of one lattice; lx and ly load the x and y
+// spinor of (site, rr).  lds: phi[12][256], acc[P1][32 RS], scr[4][32 RS].
+// prow receives [P1][32][RS].
+template <int RS, typename LX, typename LY>
+__device__ __forceinline__ void bilin_groups(const LatDesc& ld, int P1, int g0, int g1, char* lds, LX&& lx, LY&& ly,
+                                             double* __restrict__ prow) {
+    constexpr int NQ = 32 * RS;
+    double2* const phi = reinterpret_cast<double2*>(lds);
+    double* const acc = reinterpret_cast<double*>(phi + 12 * 256);
+    double* const scr = acc + (size_t)P1 * NQ;
+    const int lane = threadIdx.x;
+    const int Lz = ld.L[2], sz = ld.L[0] * ld.L[1], ncols = sz * ld.L[3];
+    const int ncol = 256 / (RS * Lz);
+    const int rr = lane & (RS - 1), q = lane / RS;
+    const int z = q / ncol, cl = q - z * ncol;
+    const bool in = z < Lz;
+    const int nb = !in ? lane : z == Lz - 1 ? lane - (Lz - 1) * ncol * RS : lane + ncol * RS;
+    double* const my = scr + (lane >> 6) * NQ;
+    for (int i = lane; i < P1 * NQ; i += 256) acc[i] = 0.0;
+    int pend = -1;  // p of the sums in scr
+    auto collect = [&] {
+        if (pend >= 0)
+            for (int i = lane; i < NQ; i += 256)
+                acc[pend * NQ + i] += (scr[i] + scr[NQ + i]) + (scr[2 * NQ + i] + scr[3 * NQ + i]);
+    };
+    for (int g = g0; g < g1; ++g) {
+        const int c = g * ncol + cl;
+        const bool on = in && c < ncols;
+        const int t = c / sz, site = (c - t * sz) + sz * (z + Lz * t);
+        double f[24], y[24], u[18];
+        if (on) {
+            lx(site, rr, f);
+            ly(site, rr, y);
+            load_link<P64, double>(ld.gauge, ld.V, 2, site, u);
+        } else {
+#pragma unroll
+            for (int k = 0; k < 24; ++k) f[k] = y[k] = 0.0;
+#pragma unroll
+            for (int k = 0; k < 18; ++k) u[k] = 0.0;
+        }
+#pragma unroll 1
+        for (int p = 0; p < P1; ++p) {
+            __syncthreads();  // phi and scr of the step before are written
+            collect();
+            double v[24];
+            if (p > 0) {
+#pragma unroll
+                for (int k = 0; k < 12; ++k) {
+                    const double2 d = phi[k * 256 + nb];
+                    v[2 * k] = d.x;
+                    v[2 * k + 1] = d.y;
+                }
+            }
+            __syncthreads();  // and read
+            if (p > 0) {
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) {
+                        double re = 0.0, im = 0.0;
+#pragma unroll
+                        for (int j = 0; j < 3; ++j) {
+                            const double ur = u[2 * (3 * i + j)], ui = u[2 * (3 * i + j) + 1];
+                            const double hr = v[2 * (3 * s + j)], hi = v[2 * (3 * s + j) + 1];
+                            re = fma_(ur, hr, re);
+                            re = fma_(-ui, hi, re);
+                            im = fma_(ur, hi, im);
+                            im = fma_(ui, hr, im);
+                        }
+                        f[2 * (3 * s + i)] = re;
+                        f[2 * (3 * s + i) + 1] = im;
+                    }
+            }
+            if (p + 1 < P1) {
+#pragma unroll
+                for (int k = 0; k < 12; ++k) phi[k * 256 + lane] = make_double2(f[2 * k], f[2 * k + 1]);
+            }
+            // M_ab of this site, halved over the lanes: first a and a + 2, then
+            // a and a + 1, then (as RS allows) the bits of b and the parts
+            double h[8];  // [b][part], a = 2 (lane bit 5) + (lane bit 4)
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                double m[4][2];
+#pragma unroll
+                for (int a = 0; a < 4; ++a) {
+                    double re = 0.0, im = 0.0;
+#pragma unroll
+                    for (int cc = 0; cc < 3; ++cc) {
+                        const double yr = y[2 * (3 * a + cc)], yi = y[2 * (3 * a + cc) + 1];
+                        const double fr = f[2 * (3 * b + cc)], fi = f[2 * (3 * b + cc) + 1];
+                        re = fma_(yr, fr, re);
+                        re = fma_(yi, fi, re);
+                        im = fma_(yr, fi, im);
+                        im = fma_(-yi, fr, im);
+                    }
+                    m[a][0] = re;
+                    m[a][1] = im;
+                }
+#pragma unroll
+                for (int k = 0; k < 2; ++k)
+                    h[2 * b + k] = halve<16>(halve<32>(m[0][k], m[2][k]), halve<32>(m[1][k], m[3][k]));
+            }
+            const int a = 2 * ((lane >> 5) & 1) + ((lane >> 4) & 1);
+            int k0 = 8 * a;  // value index 2 (4 a + b) + part of the lane's first value
+            int n = 8;
+            if constexpr (RS <= 8) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) h[k] = halve<8>(h[k], h[4 + k]);
+                k0 += (lane & 8) ? 4 : 0;
+                n = 4;
+            }
+            if constexpr (RS <= 4) {
+#pragma unroll
+                for (int k = 0; k < 2; ++k) h[k] = halve<4>(h[k], h[2 + k]);
+                k0 += (lane & 4) ? 2 : 0;
+                n = 2;
+            }
+            if constexpr (RS <= 2) {
+                h[0] = halve<2>(h[0], h[1]);
+                k0 += (lane & 2) ? 1 : 0;
+                n = 1;
+            }
+            if constexpr (RS == 1) h[0] += __shfl_xor(h[0], 1, 64);
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                if (k < n) my[(k0 + k) * RS + rr] = h[k];
+            pend = p;
+        }
+    }
+    __syncthreads();
+    collect();
+    __syncthreads();
+    for (int i = lane; i < P1 * NQ; i += 256) prow[i] = acc[i];
+}
+
+template <int RS>
+__global__ void __launch_bounds__(256) k_bilinears(Work w, Fld x, Fld yfld, Fld ysrc, const int* __restrict__ yb,
+                                                   int P1, int gpw, double* __restrict__ part) {
+    extern __shared__ uint4 lds_dyn[];
+    for_each_vwg(w, [&](const int wg_id, const int b) {
+    const BlockDesc bd = w.blocks[b];
+    const LatDesc ld = w.lats[bd.lat];
+    const int nsub = w.nr / RS;
+    const int nws = (w.wg_start[b + 1] - w.wg_start[b]) / nsub;  // workgroups per subset of RS systems
+    const int wgb = wg_id - w.wg_start[b];
+    const int sub = wgb / nws, i = wgb - sub * nws;
+    const int ncol = 256 / (RS * ld.L[2]);
+    const int ng = (ld.L[0] * ld.L[1] * ld.L[3] + ncol - 1) / ncol;
+    const size_t gs = (size_t)ld.Vf << w.lognr;
+    const int pb = yb[2 * b];
+    const uint4* ybase = pb >= 0 ? yfld.v + (size_t)w.blocks[pb].slot_off * 12 : ysrc.v + (size_t)bd.slot_off * 12;
+    const uint4* xbase = x.v + (size_t)bd.slot_off * 12;
+    bilin_groups<RS>(
+        ld, P1, i * gpw, min(ng, (i + 1) * gpw), reinterpret_cast<char*>(lds_dyn),
+        [&](int site, int rr, double* v) {
+            load_sp<P64, double, true>(xbase, nullptr, gs, ((size_t)site << w.lognr) + sub * RS + rr, v);
+        },
+        [&](int site, int rr, double* v) {
+            load_sp<P64, double, true>(ybase, nullptr, gs, ((size_t)site << w.lognr) + sub * RS + rr, v);
+        },
+        part + (size_t)wg_id * P1 * 32 * RS);
+    });
+}
+
+// M[(sys * P1 + p) * 32 + k] from the partial rows of k_bilinears; workgroup (block, p).
+__global__ void __launch_bounds__(256) k_bilin_finish(Work w, const double* __restrict__ part, double* __restrict__ M,
+                                                      int P1, int rs) {
+    __shared__ double q[32 * 16];
+    const int b = blockIdx.x, p = blockIdx.y;
+    const int nsub = w.nr / rs, nws = (w.wg_start[b + 1] - w.wg_start[b]) / nsub;
+    if (nws == 0) return;
+    const BlockDesc bd = w.blocks[b];
+    const int nq = 32 * rs;
+    for (int sub = 0; sub < nsub; ++sub) {
+        const int w0 = w.wg_start[b] + sub * nws;
+        reduce_rows(part + (size_t)p * nq, nq, w0, w0 + nws, q, P1 * nq);
+        for (int i = threadIdx.x; i < nq; i += blockDim.x)
+            M[((size_t)(bd.sys0 + sub * rs + i % rs) * P1 + p) * 32 + i / rs] = q[i];
+        __syncthreads();
+    }
+}
+
+// The sums of one pair of canonical spinors (RS = 1, no work tables), and their
+// contraction with every Gamma_n: out[p][n], as k_gamma_contract.
+__global__ void __launch_bounds__(256) k_bilin_canonical(LatDesc ld, const double2* __restrict__ x,
+                                                         const double2* __restrict__ y, int P1, int gpw,
+                                                         double* __restrict__ part) {
+    extern __shared__ uint4 lds_dyn[];
+    const int ncol = 256 / ld.L[2];
+    const int ng = (ld.L[0] * ld.L[1] * ld.L[3] + ncol - 1) / ncol;
+    auto load = [](const double2* base, int site, double* v) {
+#pragma unroll
+        for (int k = 0; k < 12; ++k) {
+            const double2 d = base[(size_t)site * 12 + k];
+            v[2 * k] = d.x;
+            v[2 * k + 1] = d.y;
+        }
+    };
+    const int i = blockIdx.x;
+    bilin_groups<1>(
+        ld, P1, i * gpw, min(ng, (i + 1) * gpw), reinterpret_cast<char*>(lds_dyn),
+        [&](int site, int, double* v) { load(x, site, v); }, [&](int site, int, double* v) { load(y, site, v); },
+        part + (size_t)i * P1 * 32);
+}
+
+__global__ void __launch_bounds__(1024) k_bilin_canonical_out(const double* __restrict__ part, int nwg, int P1,
+                                                              GammaTab gt, double* __restrict__ out) {
+    __shared__ double q[32];
+    const int p = blockIdx.x;
+    reduce_rows(part + (size_t)p * 32, 32, 0, nwg, q, P1 * 32);
+    const int n = threadIdx.x;
+    if (n >= 16) return;
+    double re = 0.0, im = 0.0;
+    for (int a = 0; a < 4; ++a) gamma_term(gt, n, a, q, re, im);
+    out[2 * (p * 16 + n)] = re;
+    out[2 * (p * 16 + n) + 1] = im;
+}
+
 // ------------------------------------------------------------------ displacement + bilinear
 
 // phi(x) = U_z(x) phi_in(x + z) per spin (colour product), or phi_in(x) at p = 0;
@@ -998,8 +1273,7 @@ __global__ void k_displace1(double* __restrict__ out, const double* __restrict__
 }
 
 
-// X[level][sample][n][p] = coef * sum_a Gamma_n[a, perm_n(a)] * sy_a * M_{a, perm_n(a)}:
-// every Gamma_n of the DeGrand-Rossi basis has one nonzero (a power of i) per row.
+// X[level][sample][n][p] = coef * sum_a Gamma_n[a, perm_n(a)] * sy_a * M_{a, perm_n(a)}.
 // sy_a = -1 for a >= 2 when y carries a gamma_5 (y = g5 (D+sigma)^-1 g5 z).
 __global__ void k_gamma_contract(const double* __restrict__ M, int P1, int nsys, const XMap* __restrict__ xm,
                                  GammaTab gt, double* __restrict__ X, int n_noise) {
@@ -1013,17 +1287,10 @@ __global__ void k_gamma_contract(const double* __restrict__ M, int P1, int nsys,
     const double* Mp = M + ((size_t)sys * P1 + p) * 32;
     double re = 0.0, im = 0.0;
     for (int a = 0; a < 4; ++a) {
-        const int c = gt.perm[n][a];
-        double mr = Mp[2 * (4 * a + c)], mi = Mp[2 * (4 * a + c) + 1];
-        if (m.g5 && a >= 2) {
-            mr = -mr;
-            mi = -mi;
-        }
-        const int ph = gt.ph[n][a];
-        const double gr = ph == 0 ? 1.0 : ph == 2 ? -1.0 : 0.0;
-        const double gi = ph == 1 ? 1.0 : ph == 3 ? -1.0 : 0.0;
-        re += gr * mr - gi * mi;
-        im += gr * mi + gi * mr;
+        double gr = 0.0, gi = 0.0;
+        gamma_term(gt, n, a, Mp, gr, gi);
+        re += m.g5 && a >= 2 ? -gr : gr;
+        im += m.g5 && a >= 2 ? -gi : gi;
     }
     const size_t o = (((size_t)m.level * n_noise + m.sample) * 16 + n) * P1 + p;
     X[2 * o] = m.coef * re;
@@ -1196,6 +1463,38 @@ void launch_noise_block(int prec, const Work& w, Fld dst, const NoiseKey* keys, 
 }
 void launch_noise_canonical(double* dst, int V, NoiseKey key, hipStream_t s) {
     hipLaunchKernelGGL(k_noise_canonical, dim3((V + 255) / 256), dim3(256), 0, s, dst, V, key);
+}
+// LDS of the fused kernel; it takes at most 64 KiB.
+static size_t bilin_lds(int rs, int P1) { return (size_t)12 * 256 * 16 + (size_t)(P1 + 4) * 32 * rs * 8; }
+
+int bilin_rs(int nr, int max_lz, int P1) {
+    int rs = nr;
+    while (rs > 1 && (rs * max_lz > 256 || bilin_lds(rs, P1) > (size_t)64 * 1024)) rs >>= 1;
+    return rs * max_lz <= 256 && bilin_lds(rs, P1) <= (size_t)64 * 1024 ? rs : 0;
+}
+long long bilin_groups_of(const int* L, int rs) {
+    const int ncol = 256 / (rs * L[2]);
+    return ((long long)L[0] * L[1] * L[3] + ncol - 1) / ncol;
+}
+void launch_bilinears(const Work& w, int rs, int gpw, int P1, Fld x, Fld yfld, Fld ysrc, const int* yb, double* part,
+                      double* M, hipStream_t s) {
+    const dim3 grid((w.total_wg + 7) / 8 * 8);
+    const size_t lds = bilin_lds(rs, P1);
+    switch (rs) {
+        case 1: hipLaunchKernelGGL(k_bilinears<1>, grid, dim3(256), lds, s, w, x, yfld, ysrc, yb, P1, gpw, part); break;
+        case 2: hipLaunchKernelGGL(k_bilinears<2>, grid, dim3(256), lds, s, w, x, yfld, ysrc, yb, P1, gpw, part); break;
+        case 4: hipLaunchKernelGGL(k_bilinears<4>, grid, dim3(256), lds, s, w, x, yfld, ysrc, yb, P1, gpw, part); break;
+        case 8: hipLaunchKernelGGL(k_bilinears<8>, grid, dim3(256), lds, s, w, x, yfld, ysrc, yb, P1, gpw, part); break;
+        case 16: hipLaunchKernelGGL(k_bilinears<16>, grid, dim3(256), lds, s, w, x, yfld, ysrc, yb, P1, gpw, part); break;
+        default: break;
+    }
+    hipLaunchKernelGGL(k_bilin_finish, dim3(w.nblk, P1), dim3(256), 0, s, w, part, M, P1, rs);
+}
+void launch_bilin_canonical(const LatDesc& ld, const double* x, const double* y, int P1, int gpw, int nwg, double* part,
+                            const GammaTab& gt, double* out, hipStream_t s) {
+    hipLaunchKernelGGL(k_bilin_canonical, dim3(nwg), dim3(256), bilin_lds(1, P1), s, ld,
+                       reinterpret_cast<const double2*>(x), reinterpret_cast<const double2*>(y), P1, gpw, part);
+    hipLaunchKernelGGL(k_bilin_canonical_out, dim3(P1), dim3(1024), 0, s, part, nwg, P1, gt, out);
 }
 void launch_hop_reduce(const Work& w, int p, Fld phi_out, Fld phi_in, Fld yfld, Fld ysrc, const int* yb,
                        double* part, hipStream_t s) {

@@ -516,12 +516,16 @@ __device__ __forceinline__ void block_partials(double (&v)[ND], int nr, double* 
     __syncthreads();  // red[] is reused by the next virtual workgroup of a persistent launch
 }
 
-// Reduce part rows [w0, w1) of width nq into out[q] (shared), fixed order.
-// Must be called by all threads of a 256-thread workgroup.
+// Sum the nq columns of part rows [w0, w1) (rows of `stride` doubles, 0 = nq)
+// into out[q] (shared), fixed order.  Must be called by all threads of the
+// workgroup (at most 1024).  Each thread sums one run of rows of one column in
+// four interleaved sums: with a single chain every load waits for the one
+// before it, and the launch is nothing but that latency.
 __device__ __forceinline__ void reduce_rows(const double* __restrict__ part, int nq, int w0, int w1,
-                                            double* __restrict__ out /* shared, nq */) {
-    __shared__ double tmp[256];
+                                            double* __restrict__ out /* shared, nq */, int stride = 0) {
+    __shared__ double tmp[1024];
     const int T = blockDim.x;
+    const size_t rs = (size_t)(stride ? stride : nq);
     for (int q0 = 0; q0 < nq; q0 += T) {
         int nqc = min(T, nq - q0);
         int nqp = 1;
@@ -534,7 +538,17 @@ __device__ __forceinline__ void reduce_rows(const double* __restrict__ part, int
         if (q < nqc && c < C) {
             int a = w0 + (int)((long long)cnt * c / C);
             int b = w0 + (int)((long long)cnt * (c + 1) / C);
-            for (int w = a; w < b; ++w) s += part[(size_t)w * nq + q0 + q];
+            const double* pp = part + q0 + q;
+            double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+            int w = a;
+            for (; w + 4 <= b; w += 4) {
+                s0 += pp[(size_t)w * rs];
+                s1 += pp[(size_t)(w + 1) * rs];
+                s2 += pp[(size_t)(w + 2) * rs];
+                s3 += pp[(size_t)(w + 3) * rs];
+            }
+            for (; w < b; ++w) s0 += pp[(size_t)w * rs];
+            s = (s0 + s1) + (s2 + s3);
         }
         tmp[threadIdx.x] = s;
         __syncthreads();

@@ -367,6 +367,18 @@ void launch_hop_reduce(const Work& w, int p, Fld phi_out, Fld phi_in, Fld yfld, 
 // reduce hop partials to M[sys][16 complex] for one p
 void launch_hop_finish(const Work& w, const double* part, double* M, int M_stride, int p, hipStream_t s);
 
+// The same sums for every p = 0..P1-1 in one pass over the fields, into
+// M[(sys * P1 + p) * 32 + k].  bilin_rs: systems per workgroup for blocks of nr
+// systems on lattices of at most max_lz z-slices; 0 where the fused kernel
+// cannot run (a z-line of one system exceeds a workgroup, or the sums of all p
+// the LDS), and the one-hop launches above do it.  w: wg_start gives each block
+// (nr / rs) x ceil(bilin_groups_of / gpw) workgroups, or none; part holds
+// total_wg x P1 x 32 x rs doubles.
+int bilin_rs(int nr, int max_lz, int P1);
+long long bilin_groups_of(const int* L, int rs);
+void launch_bilinears(const Work& w, int rs, int gpw, int P1, Fld x, Fld yfld, Fld ysrc, const int* yb, double* part,
+                      double* M, hipStream_t s);
+
 // plain single-lattice displacement (canonical in/out, FP64) used by fs_displace
 void launch_displace_canonical(double* out, const double* in, const double* gauge64, LatDesc ld,
                                hipStream_t s);
@@ -383,6 +395,10 @@ struct GammaTab {      // Gamma_n row a: single nonzero i^ph[n][a] at column per
     int8_t perm[16][4];
     int8_t ph[16][4];
 };
+// One pair of canonical spinors: out[p][n] = y^+ Gamma_n Omega_p x (device, complex),
+// by nwg = ceil(bilin_groups_of(L, 1) / gpw) workgroups; part holds nwg x P1 x 32 doubles.
+void launch_bilin_canonical(const LatDesc& ld, const double* x, const double* y, int P1, int gpw, int nwg, double* part,
+                            const GammaTab& gt, double* out, hipStream_t s);
 void launch_gamma_contract(const double* M, int P1, int nsys, const XMap* xm, const GammaTab& gt, double* X,
                            int n_noise, hipStream_t s);
 // n_level: NULL or device [L1] sample counts per level (each <= n_noise, the slot stride)
