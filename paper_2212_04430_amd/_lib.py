@@ -173,6 +173,16 @@ def _ptr(a):
     return C.c_void_p(a.ctypes.data), 0
 
 
+def _torch_ready(a):
+    """Waits for the work that torch has issued on a device tensor's current stream: the library works on its
+    context's stream, and a short call can start before torch has written its inputs, or while torch still reads
+    the memory it gives out for the result."""
+    if _is_torch(a) and a.is_cuda:
+        st = torch.cuda.current_stream(a.device)
+        if not st.query():
+            st.synchronize()
+
+
 def _host_c128(a):
     return np.ascontiguousarray(a, dtype=np.complex128)
 
@@ -261,6 +271,7 @@ def fs_apply_dirac(ctx, m0, sigma, storage, psi):
     out = _like(psi, tuple(psi.shape))
     pi, dev = _ptr(psi)
     po, _ = _ptr(out)
+    _torch_ready(psi)
     _check(_lib.fs_apply_dirac(ctx, float(m0), float(sigma), _prec(storage), pi, po, n, dev))
     return out
 
@@ -304,6 +315,7 @@ def fs_bilinear(ctx, p_max, y, x):
     out = np.empty((p_max + 1, 16), dtype=np.complex128)
     py, dev = _ptr(y)
     px, _ = _ptr(x)
+    _torch_ready(x)
     _check(_lib.fs_bilinear(ctx, int(p_max), py, px, C.c_void_p(out.ctypes.data), 0))
     return out
 

@@ -24,6 +24,7 @@
 #include "../../include/fsmlmc.h"
 #include "fs_clover.h"
 #include "fs_kernels.h"
+#include "fs_op.h"
 #include "fs_probe.h"
 #include "fs_shift.h"
 
@@ -2364,7 +2365,96 @@ __global__ void k_uniform_tables(BlockDesc* blocks, int* wg_start, int* wg_start
 
 size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 
-// fs_apply_dirac with every device buffer carved out of the scratch area.
+// The direct operator's plan.  FP32 links are read as two rows where the
+// block-layout stencil reads them so: SU(3) links, rhs blocks of 4 or more.
+OpPlan op_plan_of(fs_ctx c, int storage, int n_rhs) {
+    return op_plan(storage, c->dims, n_rhs, storage == P32 && c->two_rows && tuned_nr(c, storage, n_rhs) >= 4);
+}
+
+// Whether the operator runs on the canonical spinors themselves (launch_op).  A
+// stencil configuration set or tuned for this storage is the block-layout
+// stencil's and is honoured there; so are FP16 storage (see k_op) and the clover
+// term, and spinors that overlap or are not 16-byte aligned need a staged copy.
+bool op_direct(const fs_ctx_s* c, int storage, const double* in, const double* out, int n_rhs) {
+    const uintptr_t a = reinterpret_cast<uintptr_t>(in), b = reinterpret_cast<uintptr_t>(out);
+    const uintptr_t n = sizeof(double) * 24 * (uintptr_t)c->V * (uintptr_t)n_rhs;
+    return storage != P16 && c->tune.find(storage) == c->tune.end() && c->c_sw == 0.0 && ((a | b) & 15) == 0 &&
+           (a + n <= b || b + n <= a);
+}
+
+// The operator by way of block-layout fields: the plan (the tuned or set rhs
+// block, work-group size and variant; a last partial block is padded with zero
+// systems) and its buffers, carved out of one area of `bytes` bytes at base.
+struct StagedOp {
+    std::unique_ptr<Plan> pl;
+    Fld fi, fo;
+    char *blocks, *wg_start, *wg_start_d, *lat, *diag, *map;
+    size_t bytes;
+};
+
+StagedOp staged_op(fs_ctx c, int storage, int n_rhs, char* base) {
+    StagedOp o;
+    const int nr = tuned_nr(c, storage, n_rhs);
+    const int nblk = (n_rhs + nr - 1) / nr;
+    std::vector<fs_ctx_s*> lats{c};
+    std::vector<BlockDesc> blocks(nblk);
+    for (int b = 0; b < nblk; ++b) {
+        blocks[b].lat = 0;
+        blocks[b].sys0 = b * nr;
+        blocks[b].slot_off = (long long)b * c->V * nr;
+    }
+    o.pl = std::make_unique<Plan>();
+    plan_host(o.pl.get(), blocks, lats, nr, tuned_wg(c, storage), tuned_ilp(c, storage), tuned_occ(c, storage), 0);
+    // tables, then the two block-layout fields (and FP16 scales)
+    const int nsys = o.pl->nsys;
+    o.bytes = 0;
+    auto take = [&](size_t n) {
+        char* const p = base + o.bytes;
+        o.bytes += align256(n);
+        return p;
+    };
+    o.blocks = take(sizeof(BlockDesc) * nblk);
+    o.wg_start = take(sizeof(int) * (nblk + 1));
+    o.wg_start_d = take(sizeof(int) * (nblk + 1));
+    o.lat = take(sizeof(LatDesc));
+    o.diag = take(sizeof(double) * nsys);
+    o.map = take(sizeof(int) * nsys);
+    const size_t fbytes = (size_t)o.pl->total_slots * prec_group_bytes_spinor(storage);
+    const size_t nbytes = storage == P16 ? (size_t)o.pl->total_slots * sizeof(float) : 0;
+    o.fi.v = reinterpret_cast<uint4*>(take(fbytes));
+    o.fo.v = reinterpret_cast<uint4*>(take(fbytes));
+    char* const ni = take(nbytes);
+    char* const no = take(nbytes);
+    if (storage == P16) {
+        o.fi.n = reinterpret_cast<float*>(ni);
+        o.fo.n = reinterpret_cast<float*>(no);
+    }
+    o.pl->x_blocks = reinterpret_cast<const BlockDesc*>(o.blocks);
+    o.pl->x_wg_start = reinterpret_cast<const int*>(o.wg_start);
+    o.pl->x_wg_start_d = reinterpret_cast<const int*>(o.wg_start_d);
+    o.pl->x_lats = reinterpret_cast<const LatDesc*>(o.lat);
+    return o;
+}
+
+void run_staged_op(fs_ctx c, int storage, double dg, const StagedOp& o, const double* in, double* out, int n_rhs) {
+    hipStream_t s = c->stream;
+    const Plan& pl = *o.pl;
+    const int nblk = (int)pl.blocks.size();
+    const double* diag = reinterpret_cast<const double*>(o.diag);
+    const int* sys_map = reinterpret_cast<const int*>(o.map);
+    const int n_items = std::max(nblk + 1, pl.nsys);
+    hipLaunchKernelGGL(k_uniform_tables, dim3((n_items + 255) / 256), dim3(256), 0, s, (BlockDesc*)o.blocks,
+                       (int*)o.wg_start, (int*)o.wg_start_d, (LatDesc*)o.lat, (double*)o.diag, (int*)o.map, nblk,
+                       pl.nr, (long long)c->V * pl.nr, pl.wg_start[1], pl.wg_start_d[1],
+                       lat_desc(c, storage, 0, pl.two_rows), dg, n_rhs);
+    const long long stride = 24ll * c->V;
+    launch_pack(storage, pl.work(storage, false), o.fi, in, stride, sys_map, s);
+    launch_dslash(storage, D_PLAIN, pl.work(storage, false, true), o.fo, o.fi, Fld(), diag, nullptr, M_ALL, nullptr, s);
+    if (c->c_sw != 0.0) launch_clover_add(storage, pl.work(storage, false), o.fo, o.fi, s);
+    launch_unpack(storage, pl.work(storage, false), out, o.fo, stride, sys_map, s);
+}
+
+// fs_apply_dirac with every device buffer in the scratch area.
 void apply_dirac_noalloc(fs_ctx c, double m0, double sigma, int storage, const double* in, double* out, int n_rhs) {
     check_ctx(c);
     check_prec(storage);
@@ -2375,57 +2465,15 @@ void apply_dirac_noalloc(fs_ctx c, double m0, double sigma, int storage, const d
     char* base = static_cast<char*>(scratch_of(c->device));
     if (!base) fail(FS_E_STATE, "no scratch area on this device");
     hipStream_t s = c->stream;
-    const int nr = tuned_nr(c, storage, n_rhs);
-    const int nblk = (n_rhs + nr - 1) / nr;
-    std::vector<fs_ctx_s*> lats{c};
-    std::vector<BlockDesc> blocks(nblk);
-    for (int b = 0; b < nblk; ++b) {
-        blocks[b].lat = 0;
-        blocks[b].sys0 = b * nr;
-        blocks[b].slot_off = (long long)b * c->V * nr;
-    }
-    Plan pl;
-    plan_host(&pl, blocks, lats, nr, tuned_wg(c, storage), tuned_ilp(c, storage), tuned_occ(c, storage), 0);
-    // scratch layout: tables, then the two block-layout fields (and FP16 scales)
-    const int nsys = pl.nsys;
-    size_t off = 0;
-    auto take = [&](size_t n) {
-        const size_t o = off;
-        off += align256(n);
-        return o;
-    };
-    const size_t o_blocks = take(sizeof(BlockDesc) * nblk), o_ws = take(sizeof(int) * (nblk + 1)),
-                 o_wsd = take(sizeof(int) * (nblk + 1)), o_lat = take(sizeof(LatDesc)),
-                 o_diag = take(sizeof(double) * nsys), o_map = take(sizeof(int) * nsys);
-    const size_t fbytes = (size_t)pl.total_slots * prec_group_bytes_spinor(storage);
-    const size_t nbytes = storage == P16 ? (size_t)pl.total_slots * sizeof(float) : 0;
-    const size_t o_fi = take(fbytes), o_fo = take(fbytes), o_ni = take(nbytes), o_no = take(nbytes);
-    if (off > kScratchBytes)
-        fail(FS_E_ARG, "input too large for the allocation-free scratch (" + std::to_string(off >> 20) +
+    // the limit holds for every call, whichever kernel runs
+    const StagedOp o = staged_op(c, storage, n_rhs, base);
+    if (o.bytes > kScratchBytes)
+        fail(FS_E_ARG, "input too large for the allocation-free scratch (" + std::to_string(o.bytes >> 20) +
                            " MiB needed, 64 MiB available)");
-    pl.x_blocks = reinterpret_cast<const BlockDesc*>(base + o_blocks);
-    pl.x_wg_start = reinterpret_cast<const int*>(base + o_ws);
-    pl.x_wg_start_d = reinterpret_cast<const int*>(base + o_wsd);
-    pl.x_lats = reinterpret_cast<const LatDesc*>(base + o_lat);
-    const double* diag = reinterpret_cast<const double*>(base + o_diag);
-    const int* sys_map = reinterpret_cast<const int*>(base + o_map);
-    Fld fi, fo;
-    fi.v = reinterpret_cast<uint4*>(base + o_fi);
-    fo.v = reinterpret_cast<uint4*>(base + o_fo);
-    if (storage == P16) {
-        fi.n = reinterpret_cast<float*>(base + o_ni);
-        fo.n = reinterpret_cast<float*>(base + o_no);
-    }
-    const int n_items = std::max(nblk + 1, nsys);
-    hipLaunchKernelGGL(k_uniform_tables, dim3((n_items + 255) / 256), dim3(256), 0, s, (BlockDesc*)(base + o_blocks),
-                       (int*)(base + o_ws), (int*)(base + o_wsd), (LatDesc*)(base + o_lat), (double*)(base + o_diag),
-                       (int*)(base + o_map), nblk, nr, (long long)c->V * nr, pl.wg_start[1], pl.wg_start_d[1],
-                       lat_desc(c, storage, 0, pl.two_rows), 4.0 + m0 + sigma, n_rhs);
-    const long long stride = 24ll * c->V;
-    launch_pack(storage, pl.work(storage, false), fi, in, stride, sys_map, s);
-    launch_dslash(storage, D_PLAIN, pl.work(storage, false, true), fo, fi, Fld(), diag, nullptr, M_ALL, nullptr, s);
-    if (c->c_sw != 0.0) launch_clover_add(storage, pl.work(storage, false), fo, fi, s);
-    launch_unpack(storage, pl.work(storage, false), out, fo, stride, sys_map, s);
+    if (op_direct(c, storage, in, out, n_rhs))
+        launch_op(storage, op_plan_of(c, storage, n_rhs), lat_desc(c, storage), 4.0 + m0 + sigma, in, out, s);
+    else
+        run_staged_op(c, storage, 4.0 + m0 + sigma, o, in, out, n_rhs);
     HC(hipGetLastError());
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     HC(hipStreamIsCapturing(s, &cs));
@@ -2834,32 +2882,28 @@ fs_status fs_apply_dirac(fs_ctx c, double m0, double sigma, fs_prec storage, con
         if (n_rhs < 1) fail(FS_E_ARG, "n_rhs must be >= 1");
         DeviceScope ds(c->device);
         hipStream_t s = c->stream;
-        // the tuned (or set) rhs block and work-group size; a last partial
-        // block is padded with zero systems
-        const int nr = tuned_nr(c, storage, n_rhs);
-        const int nblk = (n_rhs + nr - 1) / nr;
-        std::vector<int> blk_lat(nblk, 0);
-        std::vector<fs_ctx_s*> lats{c};
-        auto pl = make_plan(blk_lat, lats, nr, tuned_wg(c, storage), s, tuned_ilp(c, storage), tuned_occ(c, storage));
-        std::vector<int> sys_map(pl->nsys);
-        for (int i = 0; i < pl->nsys; ++i) sys_map[i] = i < n_rhs ? i : -1;
-        DevBuf d_map = to_device(sys_map.data(), sizeof(int) * sys_map.size(), 0, s);
         const size_t nb = sizeof(double) * 24 * (size_t)c->V * n_rhs;
-        DevBuf din = to_device(in, nb, is_device, s);
-        DevBuf dout(nb);
-        Field fi, fo;
-        fi.alloc(storage, pl->total_slots);
-        fo.alloc(storage, pl->total_slots);
-        const long long stride = 24ll * c->V;
-        launch_pack(storage, pl->work(storage, false), fi.f(), din.as<double>(), stride, d_map.as<int>(), s);
-        std::vector<double> diag(pl->nsys, 4.0 + m0 + sigma);
-        DevBuf d_diag = to_device(diag.data(), sizeof(double) * diag.size(), 0, s);
-        launch_dslash(storage, D_PLAIN, pl->work(storage, false, true), fo.f(), fi.f(), Fld(), d_diag.as<double>(),
-                      nullptr, M_ALL, nullptr, s);
-        if (c->c_sw != 0.0) launch_clover_add(storage, pl->work(storage, false), fo.f(), fi.f(), s);
-        launch_unpack(storage, pl->work(storage, false), dout.as<double>(), fo.f(), stride, d_map.as<int>(), s);
+        DevBuf din, dout;
+        const double* vi = in;
+        double* vo = out;
+        if (!is_device) {
+            din = to_device(in, nb, 0, s);
+            dout.alloc(nb);
+            vi = din.as<double>();
+            vo = dout.as<double>();
+        }
+        if (op_direct(c, storage, vi, vo, n_rhs)) {
+            launch_op(storage, op_plan_of(c, storage, n_rhs), lat_desc(c, storage), 4.0 + m0 + sigma, vi, vo, s);
+            HC(hipGetLastError());
+            if (!is_device) from_device(out, dout, nb, 0, s);
+            else HC(hipStreamSynchronize(s));
+            return;
+        }
+        DevBuf work(staged_op(c, storage, n_rhs, nullptr).bytes);
+        run_staged_op(c, storage, 4.0 + m0 + sigma, staged_op(c, storage, n_rhs, work.as<char>()), vi, vo, n_rhs);
         HC(hipGetLastError());
-        from_device(out, dout, nb, is_device, s);
+        if (!is_device) from_device(out, dout, nb, 0, s);
+        else HC(hipStreamSynchronize(s));
     });
 }
 

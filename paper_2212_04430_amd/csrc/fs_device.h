@@ -300,6 +300,47 @@ __device__ __forceinline__ void load_link(const void* __restrict__ gauge, int V,
     }
 }
 
+// Row 2 of a special unitary 3x3 matrix from rows 0 and 1: the complex
+// conjugate of their cross product, U_2j = conj(U_0k U_1l - U_0l U_1k) with
+// (j, k, l) a cyclic permutation of (0, 1, 2).  u holds the matrix row-major
+// as (re, im) pairs; u[12..17] is overwritten.
+template <typename A>
+__device__ __forceinline__ void su3_third_row(A u[18]) {
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        const int k = (j + 1) % 3, l = (j + 2) % 3;
+        const A akr = u[2 * k], aki = u[2 * k + 1], alr = u[2 * l], ali = u[2 * l + 1];
+        const A bkr = u[6 + 2 * k], bki = u[7 + 2 * k], blr = u[6 + 2 * l], bli = u[7 + 2 * l];
+        // re = akr blr - aki bli - alr bkr + ali bki, -im = -(akr bli + aki blr - alr bki - ali bkr),
+        // each one multiply-add chain
+        A re = akr * blr;
+        re = fma_(-aki, bli, re);
+        re = fma_(-alr, bkr, re);
+        re = fma_(ali, bki, re);
+        A nim = -akr * bli;
+        nim = fma_(-aki, blr, nim);
+        nim = fma_(alr, bki, nim);
+        nim = fma_(ali, bkr, nim);
+        u[12 + 2 * j] = re;
+        u[13 + 2 * j] = nim;
+    }
+}
+
+// FP32 link of a lattice of special unitary links as rows 0 and 1 of the same
+// planes, row 2 rebuilt: the values of the two-row quad-shared load below.
+__device__ __forceinline__ void load_link_rows(const void* __restrict__ gauge, int V, int mu, int site, float u[18]) {
+    const uint32_t plane = uni((uint32_t)V * 8u);
+    const auto rs = buf_rsrc(reinterpret_cast<const char*>(gauge) + (size_t)mu * 9 * plane, 9 * plane);
+    const uint32_t off = (uint32_t)site * 8u;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        const auto q = __builtin_amdgcn_raw_buffer_load_b64(rs, off, k * plane, 0);
+        u[2 * k] = __uint_as_float(q[0]);
+        u[2 * k + 1] = __uint_as_float(q[1]);
+    }
+    su3_third_row<float>(u);
+}
+
 // Quad-shared link load.  When the four lanes of a quad hold four systems of
 // the same site (rhs blocks of 4 or more), each lane loads one 16-byte chunk of
 // the site-major link, so a quad reads one contiguous window per instruction,
@@ -329,32 +370,6 @@ __device__ __forceinline__ void load_words9_q(__amdgpu_buffer_rsrc_t rs, uint32_
         w[k] = quad_bcast<0>(q[k]);
         w[3 + k] = quad_bcast<1>(q[k]);
         w[6 + k] = quad_bcast<2>(q[k]);
-    }
-}
-
-// Row 2 of a special unitary 3x3 matrix from rows 0 and 1: the complex
-// conjugate of their cross product, U_2j = conj(U_0k U_1l - U_0l U_1k) with
-// (j, k, l) a cyclic permutation of (0, 1, 2).  u holds the matrix row-major
-// as (re, im) pairs; u[12..17] is overwritten.
-template <typename A>
-__device__ __forceinline__ void su3_third_row(A u[18]) {
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-        const int k = (j + 1) % 3, l = (j + 2) % 3;
-        const A akr = u[2 * k], aki = u[2 * k + 1], alr = u[2 * l], ali = u[2 * l + 1];
-        const A bkr = u[6 + 2 * k], bki = u[7 + 2 * k], blr = u[6 + 2 * l], bli = u[7 + 2 * l];
-        // re = akr blr - aki bli - alr bkr + ali bki, -im = -(akr bli + aki blr - alr bki - ali bkr),
-        // each one multiply-add chain
-        A re = akr * blr;
-        re = fma_(-aki, bli, re);
-        re = fma_(-alr, bkr, re);
-        re = fma_(ali, bki, re);
-        A nim = -akr * bli;
-        nim = fma_(-aki, blr, nim);
-        nim = fma_(alr, bki, nim);
-        nim = fma_(ali, bkr, nim);
-        u[12 + 2 * j] = re;
-        u[13 + 2 * j] = nim;
     }
 }
 
@@ -440,10 +455,12 @@ __device__ __forceinline__ void load_link_q(const void* __restrict__ gauge_q, in
 
 // Link load of the stencil, by variant Q: 0 one component per load (rhs
 // blocks of 1 or 2), 1 quad-shared whole links, 2 quad-shared rows 0-1 with
-// row 2 rebuilt (FP32; every lattice of the plan holds special unitary links).
+// row 2 rebuilt (FP32; every lattice of the plan holds special unitary links), 3
+// the same values by one component per load.
 template <int P, int Q, typename A>
 __device__ __forceinline__ void link(const LatDesc& ld, int mu, int site, A u[18]) {
     if constexpr (Q == 2) load_link_q2<P, A>(ld.gauge_q, ld.V, mu, site, u);
+    else if constexpr (Q == 3) load_link_rows(ld.gauge, ld.V, mu, site, u);
     else if constexpr (Q == 1) load_link_q<P, A>(ld.gauge_q, ld.V, mu, site, u);
     else load_link<P, A>(ld.gauge, ld.V, mu, site, u);
 }
