@@ -1060,15 +1060,28 @@ struct BatchSolver {
         x.blk_on = flags;
         return x;
     }
-    // persistent launch over the blocks of list vl (tile or stencil mapping)
-    Work listed(const VList& vl, int P, bool stencil) const {
+    // Whether launches walk a device-side list of their blocks.  The list costs a
+    // launch of its own after every change; a plan whose workgroups run in about
+    // two rounds at most is launched whole instead, and the workgroups of blocks
+    // without work leave after reading their block's flag.
+    // (Clover sampling on 12^3x24, up to 6100 workgroups: 72.5 ms with lists above
+    // 2048, 84.2 ms with the same launches whole.)
+    bool lists() const { return cur->max_wg() > 2048; }
+    // launch over the blocks of list vl, or of the flags it is built from (tile
+    // or stencil mapping)
+    Work listed(const VList& vl, int P, bool stencil) {
         Work x = cur->work(P, false, stencil);
+        if (!lists()) {
+            x.blk_on = vl.list == vl_run.list ? f_run() : vl.list == vl_pend.list ? f_pend() : f_conv();
+            return x;
+        }
         x.vlist = vl.list;
         x.vstart = stencil ? vl.vstart_sten : vl.vstart_tile;
         x.vcount = vl.count;
         return x;
     }
     void build_list(const int* flags, const VList& vl) {
+        if (!lists()) return;
         launch_vlist(flags, (int)cur->blocks.size(), cur->d_wg_start.as<int>(), cur->d_wg_start_d.as<int>(), vl, s);
     }
 
@@ -1080,7 +1093,7 @@ struct BatchSolver {
     // |r|^2, and one vector kernel updates x, r and p (8 field passes; with
     // s = r - alpha v, 11 per iteration besides the stencils).
     // With in_loop_reliable the FP64 reliable update of the blocks that asked
-    // for one follows at once (no host round trip).
+    // for one follows (no host round trip).
     void iteration(bool in_loop_reliable) {
         const Work wr = listed(vl_run, o.P, false), wd = listed(vl_run, o.P, true);
         apply(o.P, D_RHAT, wd, v.f(), p.f(), Fld(), M_RUN, tmp.f());
@@ -1186,6 +1199,14 @@ struct BatchSolver {
         // the only FP64 check is at convergence, driven from the host.
         const bool in_loop = o.P != P64;
         const int k = std::max(1, o.check_every);
+        // Reliable updates run after every fourth iteration and at the end of a
+        // chunk: a system that asks for one between waits, its own sequence of
+        // operations unchanged.  Updates asked for in different iterations then
+        // share the FP64 launches (432-system FP32 estimate on 16^3x32 602 -> 583
+        // ms) and small solves skip the empty ones (8^3x12, six FP32 systems 5.8
+        // -> 4.8 ms; every second 580 and 5.2, every eighth 590 and 5.2).
+        constexpr int kRelEvery = 4;
+        auto rel_after = [&](int i) { return in_loop && ((i + 1) % kRelEvery == 0 || i + 1 == k); };
         hipGraphExec_t exec = nullptr;
         hipGraph_t graph = nullptr;
         auto drop_graph = [&]() {
@@ -1196,7 +1217,7 @@ struct BatchSolver {
         };
         auto capture = [&]() {
             HC(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-            for (int i = 0; i < k; ++i) iteration(in_loop);
+            for (int i = 0; i < k; ++i) iteration(rel_after(i));
             dslash_calls -= 2 * k;
             HC(hipStreamEndCapture(s, &graph));
             HC(hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0));
@@ -1210,7 +1231,7 @@ struct BatchSolver {
                     HC(hipGraphLaunch(exec, s));
                     dslash_calls += 2 * k;
                 } else {
-                    for (int i = 0; i < k; ++i) iteration(in_loop);
+                    for (int i = 0; i < k; ++i) iteration(rel_after(i));
                 }
                 HC(hipMemcpyAsync(st_host.data(), d_st.p, sizeof(SysState) * pl.nsys, hipMemcpyDeviceToHost, s));
                 HC(hipStreamSynchronize(s));

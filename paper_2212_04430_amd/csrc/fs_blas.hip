@@ -488,8 +488,8 @@ __device__ __forceinline__ void finish_system(SysState& S, const double* q, int 
 // reliable update (the other stages write 0 there, clearing the flags they
 // consumed).
 template <int STAGE>
-__global__ void __launch_bounds__(256) k_finish(Work w, SysState* __restrict__ st, const double* __restrict__ part,
-                                                int* __restrict__ blk_on, int* __restrict__ blk_pend) {
+__global__ void __launch_bounds__(1024) k_finish(Work w, SysState* __restrict__ st, const double* __restrict__ part,
+                                                 int* __restrict__ blk_on, int* __restrict__ blk_pend) {
     constexpr int ND = STAGE == F_INIT ? 4 : STAGE == F_ALPHA ? 2 : STAGE == F_OMEGA ? 8
                      : (STAGE == F_TRUE || STAGE == F_BNORM) ? 1 : 3;
     __shared__ double q[ND * 16];
@@ -501,7 +501,7 @@ __global__ void __launch_bounds__(256) k_finish(Work w, SysState* __restrict__ s
     for (int kk = w.vlist ? (int)blockIdx.x : 0; kk < nlist; kk += w.vlist ? (int)gridDim.x : 1) {
     const int b = w.vlist ? w.vlist[kk] : (int)blockIdx.x;
     const BlockDesc bd = w.blocks[b];
-    if (!w.vlist && w.blk_on && !w.blk_on[b] && STAGE != F_INIT) return;
+    if (!w.vlist && w.blk_on && !w.blk_on[b] && STAGE != F_INIT) break;
     const int M = w.prow > 1 ? w.prow : 1;  // partial rows per workgroup of the mapping
     reduce_rows(part, ND * nr, w.wg_start[b] * M, w.wg_start[b + 1] * M, q);
     if (threadIdx.x == 0) {
@@ -552,53 +552,53 @@ __global__ void k_blk_mask(Work w, const SysState* __restrict__ st, int mask, in
 
 // Compact the blocks with flags[b] != 0 into a list (block order) with the
 // prefix sums of their workgroup counts in both mappings.  One workgroup.
-__global__ void __launch_bounds__(256) k_vlist(const int* __restrict__ flags, int nblk, const int* __restrict__ wg_tile,
-                                               const int* __restrict__ wg_sten, VList out) {
-    __shared__ int sc[256], st[256], ss[256];
-    __shared__ int base_n, base_t, base_s;
-    if (threadIdx.x == 0) {
-        base_n = 0;
-        base_t = 0;
-        base_s = 0;
-    }
+__global__ void __launch_bounds__(1024) k_vlist(const int* __restrict__ flags, int nblk,
+                                                const int* __restrict__ wg_tile, const int* __restrict__ wg_sten,
+                                                VList out) {
+    __shared__ int wsum[3][16];
+    __shared__ int base[3];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwave = blockDim.x >> 6;
+    if (threadIdx.x < 3) base[threadIdx.x] = 0;
     __syncthreads();
-    for (int c0 = 0; c0 < nblk; c0 += 256) {
+    for (int c0 = 0; c0 < nblk; c0 += blockDim.x) {
         const int b = c0 + threadIdx.x;
-        const int on = (b < nblk && flags[b]) ? 1 : 0;
+        const int on = b < nblk && flags[b] ? 1 : 0;
         const int ct = on ? wg_tile[b + 1] - wg_tile[b] : 0;
         const int cs = on ? wg_sten[b + 1] - wg_sten[b] : 0;
-        sc[threadIdx.x] = on;
-        st[threadIdx.x] = ct;
-        ss[threadIdx.x] = cs;
+        int v[3] = {on, ct, cs};
+        for (int off = 1; off < 64; off <<= 1) {  // inclusive scan of the wave
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const int u = __shfl_up(v[k], off, 64);
+                if (lane >= off) v[k] += u;
+            }
+        }
+        if (lane == 63) {
+#pragma unroll
+            for (int k = 0; k < 3; ++k) wsum[k][wave] = v[k];
+        }
         __syncthreads();
-        for (int off = 1; off < 256; off <<= 1) {  // inclusive scan (Hillis-Steele)
-            const int a0 = threadIdx.x >= off ? sc[threadIdx.x - off] : 0;
-            const int a1 = threadIdx.x >= off ? st[threadIdx.x - off] : 0;
-            const int a2 = threadIdx.x >= off ? ss[threadIdx.x - off] : 0;
-            __syncthreads();
-            sc[threadIdx.x] += a0;
-            st[threadIdx.x] += a1;
-            ss[threadIdx.x] += a2;
-            __syncthreads();
+        int before[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            before[k] = base[k];
+            for (int w = 0; w < wave; ++w) before[k] += wsum[k][w];
         }
         if (on) {
-            const int k = base_n + sc[threadIdx.x] - 1;
+            const int k = before[0] + v[0] - 1;
             out.list[k] = b;
-            out.vstart_tile[k] = base_t + st[threadIdx.x] - ct;
-            out.vstart_sten[k] = base_s + ss[threadIdx.x] - cs;
+            out.vstart_tile[k] = before[1] + v[1] - ct;
+            out.vstart_sten[k] = before[2] + v[2] - cs;
         }
         __syncthreads();
-        if (threadIdx.x == 255) {
-            base_n += sc[255];
-            base_t += st[255];
-            base_s += ss[255];
-        }
+        if (threadIdx.x < 3)
+            for (int w = 0; w < nwave; ++w) base[threadIdx.x] += wsum[threadIdx.x][w];
         __syncthreads();
     }
     if (threadIdx.x == 0) {
-        out.vstart_tile[base_n] = base_t;
-        out.vstart_sten[base_n] = base_s;
-        *out.count = base_n;
+        out.vstart_tile[base[0]] = base[1];
+        out.vstart_sten[base[0]] = base[2];
+        *out.count = base[0];
     }
 }
 
@@ -1357,7 +1357,7 @@ __global__ void __launch_bounds__(256) k_copy(uint4* __restrict__ dst, const uin
 
 // ------------------------------------------------------------------ launchers
 
-static int grid_of(const Work& w) { return w.vlist ? persistent_grid(w.wg) : (w.total_wg + 7) / 8 * 8; }
+static int grid_of(const Work& w) { return launch_grid(w); }
 
 #define FS_DISPATCH_P(prec, CALL)          \
     switch (prec) {                         \
@@ -1405,21 +1405,29 @@ void launch_init(int prec, const Work& w, Fld b, Fld xhi, Fld xlo, Fld rhi, Fld 
 void launch_finish(int stage, const Work& w, SysState* st, const double* part, int* out, int* out2, hipStream_t s) {
     Work wf = w;
     const int grid = w.vlist ? std::min(w.nblk, 1024) : w.nblk;
+    if (stage == F_INIT || stage == F_BNORM) {
+        wf.blk_on = nullptr;
+        wf.vlist = nullptr;
+    }
+    // few blocks of many rows: 16 waves share the rows of one
+    const dim3 wg(w.nblk <= 256 && w.total_wg >= 64 * w.nblk ? 1024 : 256);
+#define FS_FIN(S) case S: hipLaunchKernelGGL(k_finish<S>, dim3(grid), wg, 0, s, wf, st, part, out, out2); break;
     switch (stage) {
-        case F_INIT: wf.blk_on = nullptr; wf.vlist = nullptr; hipLaunchKernelGGL(k_finish<F_INIT>, dim3(grid), dim3(256), 0, s, wf, st, part, out, out2); break;
-        case F_ALPHA: hipLaunchKernelGGL(k_finish<F_ALPHA>, dim3(grid), dim3(256), 0, s, wf, st, part, out, out2); break;
-        case F_OMEGA: hipLaunchKernelGGL(k_finish<F_OMEGA>, dim3(grid), dim3(256), 0, s, wf, st, part, out, out2); break;
-        case F_TRUE: hipLaunchKernelGGL(k_finish<F_TRUE>, dim3(grid), dim3(256), 0, s, wf, st, part, out, out2); break;
-        case F_RESUME: hipLaunchKernelGGL(k_finish<F_RESUME>, dim3(grid), dim3(256), 0, s, wf, st, part, out, out2); break;
-        case F_BNORM: wf.blk_on = nullptr; wf.vlist = nullptr; hipLaunchKernelGGL(k_finish<F_BNORM>, dim3(grid), dim3(256), 0, s, wf, st, part, out, out2); break;
+        FS_FIN(F_INIT)
+        FS_FIN(F_ALPHA)
+        FS_FIN(F_OMEGA)
+        FS_FIN(F_TRUE)
+        FS_FIN(F_RESUME)
+        FS_FIN(F_BNORM)
         default: break;
     }
+#undef FS_FIN
 }
 void launch_blk_mask(const Work& w, const SysState* st, int mask, int* blk_on, hipStream_t s) {
     hipLaunchKernelGGL(k_blk_mask, dim3((w.nblk + 255) / 256), dim3(256), 0, s, w, st, mask, blk_on);
 }
 void launch_vlist(const int* flags, int nblk, const int* wg_tile, const int* wg_sten, VList out, hipStream_t s) {
-    hipLaunchKernelGGL(k_vlist, dim3(1), dim3(256), 0, s, flags, nblk, wg_tile, wg_sten, out);
+    hipLaunchKernelGGL(k_vlist, dim3(1), dim3(1024), 0, s, flags, nblk, wg_tile, wg_sten, out);
 }
 void launch_pack(int prec, const Work& w, Fld dst, const double* src, long long sys_stride, const int* sys_map,
                  hipStream_t s) {

@@ -409,8 +409,13 @@ void launch_dilution_sum(const double* Y, int P1, const int* g0, int G, int D, d
 void launch_blk_mask(const Work& w, const SysState* st, int mask, int* blk_on, hipStream_t s);
 // list of blocks with flags[b] != 0; wg_tile / wg_sten: the two workgroup tables of the plan
 void launch_vlist(const int* flags, int nblk, const int* wg_tile, const int* wg_sten, VList out, hipStream_t s);
-// physical grid of persistent launches
-inline int persistent_grid(int wg) { return 2048 * (256 / wg); }
+// physical grid of a launch: its workgroups, a multiple of the 8 XCDs; a listed
+// (persistent) launch takes at most 2048 of 256 threads
+inline int launch_grid(const Work& w) {
+    const int all = (w.total_wg + 7) / 8 * 8;
+    const int most = 2048 * (256 / w.wg);
+    return w.vlist && all > most ? most : all;
+}
 
 // copy kernel of known size (bandwidth calibration)
 void launch_copy(uint4* dst, const uint4* src, size_t n16, hipStream_t s);

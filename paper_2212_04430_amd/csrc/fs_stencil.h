@@ -1537,7 +1537,7 @@ __global__ void __launch_bounds__(256) k_eo_post(Work w, const BlockDesc* __rest
 
 }  // namespace
 
-static int grid_of(const Work& w) { return w.vlist ? persistent_grid(w.wg) : (w.total_wg + 7) / 8 * 8; }
+static int grid_of(const Work& w) { return launch_grid(w); }
 
 // Dynamic LDS that caps resident workgroups per CU (160 KiB of LDS per CU):
 // waves = target waves per SIMD (0 = no cap).
