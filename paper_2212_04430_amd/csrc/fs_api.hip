@@ -526,7 +526,7 @@ struct Plan {
     // one-parity plans: the t-streaming mapping (FP64 source and reconstruction)
     Work work_stream(int P) const {
         Work w = work(P, false, true);
-        if (eo && ilp == 2) {
+        if (eo && ilp >= 2) {
             w.wg_start = d_wg_start_s.as<int>();
             w.total_wg = wg_start_s.back();
             w.tc = tc_s;
@@ -585,6 +585,14 @@ static bool choose_tile(int sites, const std::vector<fs_ctx_s*>& lats, int tl[3]
 // blk_lat[b]: lattice of block b; lats: the contexts of the lattices.
 // Work tables for a given list of blocks (each block keeps its system ids and
 // field offsets, so a plan over a subset of a batch shares the batch's fields).
+// axis-split stencil (k_dslash_eo_axis): up to this many output sites times
+// systems, two waves per SIMD of the chip.  Whole solves against the t-streaming
+// variant: 4 FP64 systems on 8^3x16 (16384) 6.7 -> 5.4 ms, 24 FP32 systems on
+// 8^2x6x20 (92160) 7.4 -> 6.6 ms; from 262144 on the two are within 2 % of each other
+// (50 systems on 8^3x16 27.1 and 27.7 ms), and the streaming one loads fewer links.
+#ifndef FS_AXIS_MAX_SLOTS
+#define FS_AXIS_MAX_SLOTS (256 * 4 * 2 * 64)
+#endif
 // x-pair stencil: at least this many lanes (2 waves per SIMD of the chip),
 // else the t-streaming variant, which splits small batches finer
 #ifndef FS_PAIR_MIN_LANES
@@ -704,7 +712,15 @@ void plan_host(Plan* pl, const std::vector<BlockDesc>& blocks, const std::vector
             const fs_ctx_s* c = lats[blocks[b].lat];
             lanes += (long long)(c->V / c->dims[3] / 2) * nr;
         }
-        if (lanes < FS_PAIR_MIN_LANES || !pair_tiles(nr, wg, lats, pl->ptile)) pl->ilp = 0;
+        long long slots = 0;
+        for (int b = 0; b < nblk; ++b) slots += (long long)(lats[blocks[b].lat]->V >> 1) * nr;
+        if (slots <= FS_AXIS_MAX_SLOTS) pl->ilp = 3;
+        else if (lanes < FS_PAIR_MIN_LANES || !pair_tiles(nr, wg, lats, pl->ptile)) pl->ilp = 0;
+    }
+    if (eo && pl->ilp == 3) {  // a site's hops split over four waves: 64 slots per workgroup
+        for (int b = 0; b < nblk; ++b)
+            pl->wg_start_d[b + 1] =
+                pl->wg_start_d[b] + (int)((((long long)(lats[blocks[b].lat]->V >> 1) * nr) + 63) / 64);
     }
     if (eo && pl->ilp == 2) {
         // x-pair stencil: workgroups of TY x TZ pairs of one block walking
@@ -1156,7 +1172,7 @@ struct BatchSolver {
             if (any) keep.push_back(bd);
         }
         if (keep.empty() || keep.size() == cur->blocks.size()) return false;
-        auto np = plan_from_blocks(keep, lats, pl.nr, pl.wg, s, pl.ilp, pl.occ, pl.eo);
+        auto np = plan_from_blocks(keep, lats, pl.nr, pl.wg, s, o.eo ? o.eo_var : pl.ilp, pl.occ, pl.eo);
         if (part_need(*np) > part_doubles) {
             part_doubles = part_need(*np);
             d_part.alloc(sizeof(double) * part_doubles);

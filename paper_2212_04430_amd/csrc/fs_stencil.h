@@ -1248,6 +1248,111 @@ __global__ void __launch_bounds__(256) k_dslash_eo_t(Work w, Fld out, Fld in, Fl
     });
 }
 
+// The same operator with a site's hops split over four waves.  For small
+// problems the kernels above are one long chain of dependent loads per lane
+// (eight neighbours and links in phases, at one wave per SIMD or less: 15 to 23 us
+// for 4 systems on 8^3x16).  Here a workgroup owns 64 slots; wave mu forms both
+// hops along axis mu, the four results meet in LDS, and wave 0 adds them and
+// runs the epilogue, whose centre it loaded beforehand: two dependent loads
+// deep instead of eight, 6.8 us a hop and 8.7 to 11.3 us a Schur launch at that size.
+// Latency bound.  Modes as k_dslash_eo_t (D_HOP, and with par_out = 0 the Schur
+// modes).
+template <int P, int MODE, int Q, int CLV = 0>
+__global__ void __launch_bounds__(256) k_dslash_eo_axis(Work w, Fld out, Fld in, Fld cen, Fld aux,
+                                                        const double* __restrict__ diag,
+                                                        const SysState* __restrict__ st, int mask,
+                                                        double* __restrict__ part, const uint32_t* __restrict__ rc,
+                                                        int par_out, Clv cl) {
+    static_assert(!CLV || P == P64 || P == P32, "the clover term is kept in FP64 and FP32");
+    using A = typename Tr<P>::acc;
+    constexpr int G = Tr<P>::G;
+    constexpr int ND = NDotsEo<MODE>::v;
+    __shared__ A sums[3][24][64];  // of waves 1-3
+    for_each_vwg(w, [&](const int wg_id, const int b) {
+    const BlockDesc bd = w.blocks[b];
+    const LatDesc ld = w.lats[bd.lat];
+    const int wgb = wg_id - w.wg_start[b];
+    const size_t gs = (size_t)ld.Vf << w.lognr;
+    const uint4* ib = in.v + (size_t)bd.slot_off * G;
+    const float* inn = in.n ? in.n + bd.slot_off : nullptr;
+    uint4* ob = out.v + (size_t)bd.slot_off * G;
+    float* on = out.n ? out.n + bd.slot_off : nullptr;
+    const int lane = threadIdx.x & 63;
+    const int mu = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const size_t slot = (size_t)wgb * 64 + lane;
+    const int r = (int)(slot & (size_t)(w.nr - 1));
+    const int sys = bd.sys0 + r;
+    const bool valid = slot < gs;
+    // quad-shared links need the whole quad; then the mask gates only the dots
+    const bool act = valid && mask_ok(mask, st, sys);
+    const bool run = Q ? valid : act;
+    double acc[ND];
+#pragma unroll
+    for (int k = 0; k < ND; ++k) acc[k] = 0.0;
+    A o[24], cv[24];
+#pragma unroll
+    for (int k = 0; k < 24; ++k) o[k] = A(0);
+    if (run) {
+        const int cb = (int)(slot >> w.lognr);
+        Coord c;
+        const int site = eo_site(ld, cb, par_out, c);
+        const int sy = ld.L[0], sz = ld.L[0] * ld.L[1], stt = sz * ld.L[2];
+        if (mu == 0) {
+            if constexpr (MODE != D_HOP)
+                load_sp<P, A>(cen.v + (size_t)bd.slot_off * G, cen.n ? cen.n + bd.slot_off : nullptr, gs, slot, cv);
+            hop_dir_h<P, Q, true, 0, PxM, PxP>(ld, ib, inn, gs, site, c.x, 1, r, w.lognr, o);
+        } else if (mu == 1) {
+            hop_dir_h<P, Q, true, 1, PyM, PyP>(ld, ib, inn, gs, site, c.y, sy, r, w.lognr, o);
+        } else if (mu == 2) {
+            hop_dir_h<P, Q, true, 2, PzM, PzP>(ld, ib, inn, gs, site, c.z, sz, r, w.lognr, o);
+        } else {
+            hop_dir_h<P, Q, true, 3, PtM, PtP>(ld, ib, inn, gs, site, c.t, stt, r, w.lognr, o);
+        }
+        if (mu > 0) {
+#pragma unroll
+            for (int k = 0; k < 24; ++k) sums[mu - 1][k][lane] = o[k];
+        }
+    }
+    __syncthreads();
+    if (mu == 0 && run) {
+#pragma unroll
+        for (int k = 0; k < 24; ++k) o[k] += (sums[0][k][lane] + sums[1][k][lane]) + sums[2][k][lane];
+        const size_t cb = slot >> w.lognr;
+        if constexpr (MODE != D_HOP) {
+            const A a = (A)diag[sys];
+            if constexpr (CLV) {
+                clv_schur<P, A>(ld, cb, a, cv, o);
+            } else {
+                const A ia = A(1) / a;
+#pragma unroll
+                for (int k = 0; k < 24; ++k) o[k] = a * cv[k] - ia * o[k];
+            }
+        } else if constexpr (CLV) {
+            clv_inv<P, A>(cl, ld, sys, cb, o);
+        }
+        if constexpr (MODE == D_RESID) {
+            A bv[24];
+            load_sp<P, A>(aux.v + (size_t)bd.slot_off * G, nullptr, gs, slot, bv);
+#pragma unroll
+            for (int k = 0; k < 24; ++k) o[k] = bv[k] - o[k];
+        }
+        store_sp<P, A>(ob, on, gs, slot, o);
+        if (act) {
+            if constexpr (MODE == D_RHAT) {
+                rhat_code_dots<1, A>(rc[bd.slot_off + slot], o, o, acc, acc);
+            } else if constexpr (MODE == D_TS) {
+                ts_dots<A>(o, cv, rc[bd.slot_off + slot], acc);
+            } else if constexpr (MODE == D_RESID) {
+#pragma unroll
+                for (int k = 0; k < 24; ++k) acc[0] += (double)o[k] * (double)o[k];
+            }
+        }
+    }
+    if constexpr (MODE == D_RHAT || MODE == D_TS || MODE == D_RESID) block_partials<ND, 4>(acc, w.nr, part, wg_id);
+    else __syncthreads();  // sums is reused by the next virtual workgroup
+    });
+}
+
 // The even-odd operator over x-pairs with LDS sharing (variant 2 of the
 // one-parity plans).  Lane (r, xh, iy, iz) of a workgroup owns the pair of
 // columns x = 2 xh, 2 xh + 1 at (y, z) = tile origin + (iy, iz) for system r,
@@ -1560,6 +1665,23 @@ static void launch_eo_q(const Work& w, Fld out, Fld in, Fld cen, Fld aux, const 
                         int mask, double* part, hipStream_t s, const uint32_t* rc, int par_out,
                         Clv cl = Clv()) {
     const int q = qmode<P>(w);
+    if (w.tc > 0 && w.ilp == 3) {  // 64 slots per workgroup, a wave per axis
+        switch (q) {
+            case 2:
+                if constexpr (P == P32)
+                    hipLaunchKernelGGL((k_dslash_eo_axis<P, MODE, 2, CLV>), dim3(grid_of(w)), dim3(256), 0, s, w, out, in,
+                                       cen, aux, diag, st, mask, part, rc, par_out, cl);
+                break;
+            case 1:
+                hipLaunchKernelGGL((k_dslash_eo_axis<P, MODE, 1, CLV>), dim3(grid_of(w)), dim3(256), 0, s, w, out, in,
+                                   cen, aux, diag, st, mask, part, rc, par_out, cl);
+                break;
+            default:
+                hipLaunchKernelGGL((k_dslash_eo_axis<P, MODE, 0, CLV>), dim3(grid_of(w)), dim3(256), 0, s, w, out, in,
+                                   cen, aux, diag, st, mask, part, rc, par_out, cl);
+        }
+        return;
+    }
     if (w.tc > 0 && w.ilp == 2) {  // x-pair stencil mapping with LDS sharing
         const size_t need = (size_t)tile_nbuf<P>() * in_lds_bytes<P>() * w.wg;
         const size_t lds = std::max(need, lds_cap(w.wg, w.occ));

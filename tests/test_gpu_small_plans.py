@@ -1,0 +1,65 @@
+"""Even-odd solves of small batches, whose stencil splits each site's hops over four waves (GPU).
+
+Sizes at its edges: fewer slots (sites of one parity times systems per block) than one workgroup of 64, a last
+workgroup that is nearly empty, padded blocks, two-site axes, several blocks with their own first workgroup, and both
+sides of the 131072 slots up to which it runs.  As for the other stencils the returned x is pinned by the true residual,
+recomputed by the oracle: at most 1.5 times the tolerance that the solver reports it met.
+"""
+
+import numpy as np
+import pytest
+
+import synth
+from oracle import clover as cl, lattice as lat
+from oracle.philox import z4_noise
+
+pytestmark = pytest.mark.gpu
+
+
+def _solve(dims, storage, nr, ap, csw, n, scale=1.0, sig=(0.0, 0.6)):
+    from paper_2212_04430_amd import _lib as L
+    print(f"small plan dims={dims} {storage} nr={nr} ap={ap} csw={csw} n={n}", flush=True)
+    tol = 1e-11 if storage == "f64" else 1e-9
+    U = synth.gauge_field(dims, eps=0.3, seed=5) * scale
+    V = lat.volume(dims)
+    B = np.stack([z4_noise(V, 2, 0, 0, s) for s in range(n)])
+    ctx = L.fs_create(dims, int(ap), 0)
+    try:
+        L.fs_upload_gauge(ctx, U)
+        if csw:
+            L.fs_set_clover(ctx, csw)
+        prm = L.solve_params(0.2, tol=tol, storage=storage, batched=int(nr > 0), rhs_block=nr, even_odd=1)
+        X, stats, code = L.fs_solve_shifted(ctx, prm, list(sig), B)
+    finally:
+        L.fs_destroy(ctx)
+    assert code == 0
+    C = cl.clover_term(U, dims, csw) if csw else None
+    for i, s in enumerate(sig):
+        for r in sorted({0, n // 2, n - 1}):
+            a = (cl.clover_apply(U, X[i, r], 0.2, s, csw, dims, C=C) if csw
+                 else lat.wilson_apply(U, X[i, r], 0.2, s, dims, ap))
+            assert stats[i * n + r].true_rel_residual <= tol
+            assert np.linalg.norm(B[r] - a) <= 1.5 * tol * np.linalg.norm(B[r]), (i, r)
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "f16", "bf16"])
+@pytest.mark.parametrize("dims,nr,ap,n", [((2, 2, 2, 2), 1, True, 1), ((4, 2, 6, 2), 0, False, 1),
+                                          ((6, 2, 4, 6), 4, True, 3), ((2, 10, 2, 6), 8, False, 5),
+                                          ((4, 6, 4, 10), 16, True, 9)])
+def test_edges(storage, dims, nr, ap, n):
+    _solve(dims, storage, nr, ap, 0.0, n)
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32"])
+@pytest.mark.parametrize("dims,nr", [((4, 2, 2, 6), 1), ((6, 4, 2, 4), 4)])
+def test_clover_edges(storage, dims, nr):
+    _solve(dims, storage, nr, False, 1.2, 3)
+
+
+def test_whole_links():
+    _solve((4, 6, 2, 4), "f32", 4, False, 0.0, 3, scale=0.9)  # not special unitary
+
+
+@pytest.mark.parametrize("n", [8, 9])
+def test_at_the_rule(n):
+    _solve((16, 8, 16, 16), "f32", 4, True, 0.0, n, sig=(0.0,))  # 131072 and 196608 slots
