@@ -593,10 +593,13 @@ static bool choose_tile(int sites, const std::vector<fs_ctx_s*>& lats, int tl[3]
 #ifndef FS_AXIS_MAX_SLOTS
 #define FS_AXIS_MAX_SLOTS (256 * 4 * 2 * 64)
 #endif
-// x-pair stencil: at least this many lanes (2 waves per SIMD of the chip),
-// else the t-streaming variant, which splits small batches finer
+// x-pair stencil: at least this many lanes (pairs of columns times systems),
+// else the t-streaming variant, which splits small batches finer.  Whole solves,
+// streaming and pairs: 24 FP32 systems on 16^3x32 (49152 lanes) 64.9 and 57.4 ms,
+// 34 of 12^2x14x24 (36864) 32.2 and 31.5 ms; 50 systems on 8^3x16 (13312) 27.0 and
+// 28.9 ms.
 #ifndef FS_PAIR_MIN_LANES
-#define FS_PAIR_MIN_LANES (256 * 4 * 2 * 64)
+#define FS_PAIR_MIN_LANES (256 * 96)
 #endif
 // resident x-pair workgroups per CU assumed when sizing its t-chunks
 #ifndef FS_PAIR_WG_PER_CU

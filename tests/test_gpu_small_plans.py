@@ -63,3 +63,8 @@ def test_whole_links():
 @pytest.mark.parametrize("n", [8, 9])
 def test_at_the_rule(n):
     _solve((16, 8, 16, 16), "f32", 4, True, 0.0, n, sig=(0.0,))  # 131072 and 196608 slots
+
+
+@pytest.mark.parametrize("dims", [(16, 16, 12, 12), (16, 16, 16, 8)])
+def test_at_the_pair_rule(dims):
+    _solve(dims, "f32", 4, True, 0.0, 11, sig=(0.0,))  # 18432 and 24576 pairs of columns: streaming, x-pairs
