@@ -15,6 +15,8 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 #include <stdint.h>
 
 namespace fs {
@@ -163,23 +165,34 @@ __device__ __forceinline__ uint4 pack_d(double re, double im) {
                       (uint32_t)__double2hiint(im));
 }
 
+// base + slot; S32: with the byte offset in 32 bits, so that a uniform base stays
+// in scalar registers and one lane register serves all groups of a field.  For
+// blocks of up to 2^28 slots: every one-parity field (at most 29.8M sites, 16
+// systems).
+template <bool S32, typename T>
+__device__ __forceinline__ T* atg(T* base, size_t slot) {
+    using B = std::conditional_t<std::is_const_v<T>, const char, char>;
+    if constexpr (S32) return reinterpret_cast<T*>(reinterpret_cast<B*>(base) + (uint32_t)slot * (uint32_t)sizeof(T));
+    else return base + slot;
+}
+
 // Load / store the 24 reals of spinor (slot) from a block base.  gs = group
 // stride in 16-byte units (= V * NR).  `nrm` is the FP16 per-slot scale array.
-// NT: non-temporal accesses (see ld16).
-template <int P, typename A, bool NT = false>
+// NT: non-temporal accesses (see ld16); S32: see atg.
+template <int P, typename A, bool NT = false, bool S32 = false>
 __device__ __forceinline__ void load_sp(const uint4* __restrict__ base, const float* __restrict__ nrm,
                                         size_t gs, size_t slot, A v[24]) {
     if constexpr (P == P64) {
 #pragma unroll
         for (int g = 0; g < 12; ++g) {
-            const uint4 d = ld16<NT>(base + g * gs + slot);
+            const uint4 d = ld16<NT>(atg<S32>(base + g * gs, slot));
             v[2 * g] = (A)__hiloint2double((int)d.y, (int)d.x);
             v[2 * g + 1] = (A)__hiloint2double((int)d.w, (int)d.z);
         }
     } else if constexpr (P == P32) {
 #pragma unroll
         for (int g = 0; g < 6; ++g) {
-            const uint4 d = ld16<NT>(base + g * gs + slot);
+            const uint4 d = ld16<NT>(atg<S32>(base + g * gs, slot));
             v[4 * g] = (A)__uint_as_float(d.x);
             v[4 * g + 1] = (A)__uint_as_float(d.y);
             v[4 * g + 2] = (A)__uint_as_float(d.z);
@@ -190,7 +203,7 @@ __device__ __forceinline__ void load_sp(const uint4* __restrict__ base, const fl
         if constexpr (P == P16) s = nrm[slot];
 #pragma unroll
         for (int g = 0; g < 3; ++g) {
-            uint4 d = ld16<NT>(base + g * gs + slot);
+            uint4 d = ld16<NT>(atg<S32>(base + g * gs, slot));
             uint32_t w[4] = {d.x, d.y, d.z, d.w};
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
@@ -209,16 +222,16 @@ __device__ __forceinline__ void load_sp(const uint4* __restrict__ base, const fl
     }
 }
 
-template <int P, typename A, bool NT = false>
+template <int P, typename A, bool NT = false, bool S32 = false>
 __device__ __forceinline__ void store_sp(uint4* __restrict__ base, float* __restrict__ nrm,
                                          size_t gs, size_t slot, const A v[24]) {
     if constexpr (P == P64) {
 #pragma unroll
-        for (int g = 0; g < 12; ++g) st16<NT>(base + g * gs + slot, pack_d((double)v[2 * g], (double)v[2 * g + 1]));
+        for (int g = 0; g < 12; ++g) st16<NT>(atg<S32>(base + g * gs, slot), pack_d((double)v[2 * g], (double)v[2 * g + 1]));
     } else if constexpr (P == P32) {
 #pragma unroll
         for (int g = 0; g < 6; ++g)
-            st16<NT>(base + g * gs + slot,
+            st16<NT>(atg<S32>(base + g * gs, slot),
                      make_uint4(__float_as_uint((float)v[4 * g]), __float_as_uint((float)v[4 * g + 1]),
                                 __float_as_uint((float)v[4 * g + 2]), __float_as_uint((float)v[4 * g + 3])));
     } else {
@@ -242,7 +255,7 @@ __device__ __forceinline__ void store_sp(uint4* __restrict__ base, float* __rest
                     w[k] = (uint32_t)f_to_bf16(lo) | ((uint32_t)f_to_bf16(hi) << 16);
                 }
             }
-            st16<NT>(base + g * gs + slot, make_uint4(w[0], w[1], w[2], w[3]));
+            st16<NT>(atg<S32>(base + g * gs, slot), make_uint4(w[0], w[1], w[2], w[3]));
         }
     }
 }

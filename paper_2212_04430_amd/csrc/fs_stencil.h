@@ -60,6 +60,38 @@ __device__ __forceinline__ void ph(int code, A re, A im, A& ore, A& oim) {
 // the lower two spins of the result are i^B2 h_K2 and i^B3 h_K3.
 template <int J0, int A0, int J1, int A1, int K2, int B2, int K3, int B3>
 struct Proj {
+    // One half H (h0 or h1) by itself: a = psi_H, b = psi_J, J the spin it is
+    // combined with, and the accumulation of its product w.
+    template <int H> static constexpr int partner = H ? J1 : J0;
+    template <int H, typename A>
+    __device__ __forceinline__ static void project1(const A a[6], const A b[6], A h[6]) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            A re, im;
+            ph<A>(H ? A1 : A0, b[2 * c], b[2 * c + 1], re, im);
+            h[2 * c] = a[2 * c] + re;
+            h[2 * c + 1] = a[2 * c + 1] + im;
+        }
+    }
+    template <int H, typename A>
+    __device__ __forceinline__ static void accum1(A o[24], const A w[6], A cf) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            A re, im;
+            o[2 * (3 * H + c)] += cf * w[2 * c];
+            o[2 * (3 * H + c) + 1] += cf * w[2 * c + 1];
+            if constexpr (K2 == H) {
+                ph<A>(B2, w[2 * c], w[2 * c + 1], re, im);
+                o[2 * (6 + c)] += cf * re;
+                o[2 * (6 + c) + 1] += cf * im;
+            }
+            if constexpr (K3 == H) {
+                ph<A>(B3, w[2 * c], w[2 * c + 1], re, im);
+                o[2 * (9 + c)] += cf * re;
+                o[2 * (9 + c) + 1] += cf * im;
+            }
+        }
+    }
     template <typename A>
     __device__ __forceinline__ static void project(const A v[24], A h[12]) {
 #pragma unroll
@@ -133,50 +165,55 @@ using PtP = Proj<2, 0, 3, 0, 0, 0, 1, 0>;  // 1 + g4
 // sum a plain product.  (Written as re += ur*hr - ui*hi the compiler keeps the
 // difference as its own rounding step and spends 6.)
 template <typename A>
-__device__ __forceinline__ void mul_u(const A u[18], const A h[12], A w[12]) {
+__device__ __forceinline__ void mul_u1(const A u[18], const A hs[6], A w[6]) {
 #pragma unroll
-    for (int s = 0; s < 2; ++s)
+    for (int i = 0; i < 3; ++i) {
+        const A* ur = u + 6 * i;  // row i
+        A re = ur[0] * hs[0], im = ur[0] * hs[1];
+        re = fma_(-ur[1], hs[1], re);
+        im = fma_(ur[1], hs[0], im);
 #pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            const A* hs = h + 6 * s;
-            const A* ur = u + 6 * i;  // row i
-            A re = ur[0] * hs[0], im = ur[0] * hs[1];
-            re = fma_(-ur[1], hs[1], re);
-            im = fma_(ur[1], hs[0], im);
-#pragma unroll
-            for (int j = 1; j < 3; ++j) {
-                re = fma_(ur[2 * j], hs[2 * j], re);
-                re = fma_(-ur[2 * j + 1], hs[2 * j + 1], re);
-                im = fma_(ur[2 * j], hs[2 * j + 1], im);
-                im = fma_(ur[2 * j + 1], hs[2 * j], im);
-            }
-            w[6 * s + 2 * i] = re;
-            w[6 * s + 2 * i + 1] = im;
+        for (int j = 1; j < 3; ++j) {
+            re = fma_(ur[2 * j], hs[2 * j], re);
+            re = fma_(-ur[2 * j + 1], hs[2 * j + 1], re);
+            im = fma_(ur[2 * j], hs[2 * j + 1], im);
+            im = fma_(ur[2 * j + 1], hs[2 * j], im);
         }
+        w[2 * i] = re;
+        w[2 * i + 1] = im;
+    }
 }
 
 // The same with the Hermitian conjugate U^dagger (column i of U, conjugated).
 template <typename A>
-__device__ __forceinline__ void mul_udag(const A u[18], const A h[12], A w[12]) {
+__device__ __forceinline__ void mul_udag1(const A u[18], const A hs[6], A w[6]) {
 #pragma unroll
-    for (int s = 0; s < 2; ++s)
+    for (int i = 0; i < 3; ++i) {
+        A re = u[2 * i] * hs[0], im = u[2 * i] * hs[1];
+        re = fma_(u[2 * i + 1], hs[1], re);
+        im = fma_(-u[2 * i + 1], hs[0], im);
 #pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            const A* hs = h + 6 * s;
-            A re = u[2 * i] * hs[0], im = u[2 * i] * hs[1];
-            re = fma_(u[2 * i + 1], hs[1], re);
-            im = fma_(-u[2 * i + 1], hs[0], im);
-#pragma unroll
-            for (int j = 1; j < 3; ++j) {
-                const A cr = u[2 * (3 * j + i)], ci = u[2 * (3 * j + i) + 1];
-                re = fma_(cr, hs[2 * j], re);
-                re = fma_(ci, hs[2 * j + 1], re);
-                im = fma_(cr, hs[2 * j + 1], im);
-                im = fma_(-ci, hs[2 * j], im);
-            }
-            w[6 * s + 2 * i] = re;
-            w[6 * s + 2 * i + 1] = im;
+        for (int j = 1; j < 3; ++j) {
+            const A cr = u[2 * (3 * j + i)], ci = u[2 * (3 * j + i) + 1];
+            re = fma_(cr, hs[2 * j], re);
+            re = fma_(ci, hs[2 * j + 1], re);
+            im = fma_(cr, hs[2 * j + 1], im);
+            im = fma_(-ci, hs[2 * j], im);
         }
+        w[2 * i] = re;
+        w[2 * i + 1] = im;
+    }
+}
+
+template <typename A>
+__device__ __forceinline__ void mul_u(const A u[18], const A h[12], A w[12]) {
+    mul_u1(u, h, w);
+    mul_u1(u, h + 6, w + 6);
+}
+template <typename A>
+__device__ __forceinline__ void mul_udag(const A u[18], const A h[12], A w[12]) {
+    mul_udag1(u, h, w);
+    mul_udag1(u, h + 6, w + 6);
 }
 
 // U h for a half spinor in its packed forms hc = conj(h), hs = swap(h): each
@@ -289,13 +326,13 @@ template <> struct PairIn<P16> { using T = SpH; };
 // then [lanes] scales).
 template <int P> constexpr int in_lds_bytes() { return P == P16 ? 52 : 24 * (int)sizeof(typename Tr<P>::acc); }
 
-template <int P>
+template <int P, bool S32 = false>
 __device__ __forceinline__ void in_load(const uint4* __restrict__ ib, const float* __restrict__ inn, size_t gs,
                                         size_t slot, typename PairIn<P>::T& x) {
     if constexpr (P == P16) {
 #pragma unroll
         for (int g = 0; g < 3; ++g) {
-            const uint4 d = ld16<false>(ib + g * gs + slot);
+            const uint4 d = ld16<false>(atg<S32>(ib + g * gs, slot));
             x.w[4 * g] = d.x;
             x.w[4 * g + 1] = d.y;
             x.w[4 * g + 2] = d.z;
@@ -303,7 +340,7 @@ __device__ __forceinline__ void in_load(const uint4* __restrict__ ib, const floa
         }
         x.s = inn[slot];
     } else {
-        load_sp<P, typename Tr<P>::acc>(ib, inn, gs, slot, x.v);
+        load_sp<P, typename Tr<P>::acc, false, S32>(ib, inn, gs, slot, x.v);
     }
 }
 
@@ -1368,6 +1405,16 @@ __global__ void __launch_bounds__(256) k_dslash_eo_axis(Work w, Fld out, Fld in,
 // (the lane's other column) is formed from the pair's input site and carried
 // in registers.  Modes as k_dslash_eo_t (D_HOP, and with par_out = 0 the
 // Schur modes).
+// Bound by memory, and before that by registers: with the per-lane constants
+// kept out of registers (see the slice loop), 32-bit lane offsets and FP64 by half
+// spinors every FP64 launch runs two waves per SIMD (one, with up to 116 registers
+// in accumulation registers, before) and FP32 D_TS three (two).  No minimum of
+// waves is asked for: scheduled for one wave the loads are issued earlier, and the
+// launches fit all the same (FP32 D_TS 1.04 ms scheduled for three waves, 0.97 for one).
+// 432 systems on 16^3x32: FP32 hop 1.68 -> 1.61 ms, FP64 hop 5.39 -> 3.78 (the
+// smallest possible traffic at copy rate: 2.9); averages over a solve: FP32 D_RHAT
+// 1.01 -> 0.94 ms, D_TS 1.15 -> 0.97, FP64 residual 0.87 -> 0.75.
+//
 // One neighbour of the x-pair stencil: from LDS when it is inside the tile,
 // else from memory; every lane issues the memory load (interior lanes load
 // slot 0, a broadcast) and the value is selected, so the code has no branch.
@@ -1376,9 +1423,21 @@ __device__ __forceinline__ void pair_fetch(bool inside, const uint4* __restrict_
                                            size_t gs, size_t gslot, const char* sh, int wg, int nl,
                                            typename PairIn<P>::T& v) {
     typename PairIn<P>::T g, l;
-    in_load<P>(ib, inn, gs, inside ? (size_t)0 : gslot, g);
+    in_load<P, true>(ib, inn, gs, inside ? (size_t)0 : gslot, g);
     in_get<P>(sh, wg, nl, l);
     in_sel<P>(inside, l, g, v);
+}
+
+// Spin k of an FP64 neighbour, likewise.
+__device__ __forceinline__ void pair_spin64(bool inside, const uint4* __restrict__ ib, size_t gs, size_t gslot,
+                                            const double2* sh, int wg, int nl, int k, double v[6]) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const double2 a = *atg<true>(reinterpret_cast<const double2*>(ib) + (3 * k + c) * gs, gslot);
+        const double2 b = sh[(3 * k + c) * wg + nl];
+        v[2 * c] = inside ? b.x : a.x;
+        v[2 * c + 1] = inside ? b.y : a.y;
+    }
 }
 
 // One spatial axis of the x-pair stencil: forward and backward hops of the
@@ -1408,11 +1467,68 @@ __device__ __forceinline__ void pair_hop(const LatDesc& ld, const uint4* __restr
     }
 }
 
+// The FP64 hops of the x-pair stencil, one half spinor after the other (each needs
+// two spins of the neighbour; spin(k, v) loads spin k), with scheduling barriers
+// between them: a whole FP64 neighbour is 48 registers, and its copies from LDS
+// and from memory, side by side with the other neighbour's, took every launch
+// past 256.
+template <int Q, int H, bool FWD, typename PR, typename F>
+__device__ __forceinline__ void hop_half64(const double u[18], F&& spin, double w[6]) {
+    double a[6], b[6], h[6];
+    spin(H, a);
+    spin(PR::template partner<H>, b);
+    PR::template project1<H>(a, b, h);
+    if constexpr (FWD) mul_u1(u, h, w);
+    else mul_udag1(u, h, w);
+}
+template <int Q, bool FWD, typename PR, typename F>
+__device__ __forceinline__ void hop64(const LatDesc& ld, int mu, int lsite, F&& spin, double o[24], double cf) {
+    double u[18];
+    link<P64, Q, double>(ld, mu, lsite, u);
+    {
+        double w[6];
+        hop_half64<Q, 0, FWD, PR>(u, spin, w);
+        PR::template accum1<0>(o, w, cf);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    {
+        double w[6];
+        hop_half64<Q, 1, FWD, PR>(u, spin, w);
+        PR::template accum1<1>(o, w, cf);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+}
+template <int Q, int MU, typename PF, typename PB>
+__device__ __forceinline__ void pair_hop64(const LatDesc& ld, const uint4* __restrict__ ib, size_t gs,
+                                           const double2* sh, int wg, int lane, int i, int T, int Lm, int ls, int c,
+                                           int cb, int cstride, int so, int sstride, int r, int lognr, double o[24]) {
+    const bool whole = T == Lm;  // the tile spans the axis: wrap-around inside it
+    {
+        const int cbf = (c == Lm - 1) ? cb - (Lm - 1) * cstride : cb + cstride;
+        const bool inside = whole || i < T - 1;
+        const size_t gslot = inside ? (size_t)0 : ((size_t)cbf << lognr) + r;
+        const int nl = (i < T - 1) ? lane + ls : lane - (T - 1) * ls;
+        hop64<Q, true, PF>(ld, MU, so, [&](int k, double v[6]) {
+            pair_spin64(inside, ib, gs, gslot, sh, wg, nl, k, v);
+        }, o, -0.5);
+    }
+    {
+        const int cbb = (c == 0) ? cb + (Lm - 1) * cstride : cb - cstride;
+        const int sb = (c == 0) ? so + (Lm - 1) * sstride : so - sstride;
+        const bool inside = whole || i > 0;
+        const size_t gslot = inside ? (size_t)0 : ((size_t)cbb << lognr) + r;
+        const int nl = (i > 0) ? lane - ls : lane + (T - 1) * ls;
+        hop64<Q, false, PB>(ld, MU, sb, [&](int k, double v[6]) {
+            pair_spin64(inside, ib, gs, gslot, sh, wg, nl, k, v);
+        }, o, -0.5);
+    }
+}
 template <int P, int MODE, int Q, int CLV = 0>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TileW<P, MODE>::v, 8)))
-k_dslash_eo_pair(Work w, Fld out, Fld in, Fld cen, Fld aux, const double* __restrict__ diag,
-                 const SysState* __restrict__ st, int mask, double* __restrict__ part,
-                 const uint32_t* __restrict__ rc, int par_out, Clv cl) {
+__global__ void __launch_bounds__(256) k_dslash_eo_pair(Work w, Fld out, Fld in, Fld cen, Fld aux,
+                                                        const double* __restrict__ diag,
+                                                        const SysState* __restrict__ st, int mask,
+                                                        double* __restrict__ part, const uint32_t* __restrict__ rc,
+                                                        int par_out, Clv cl) {
     static_assert(!CLV || P == P64 || P == P32, "the clover term is kept in FP64 and FP32");
     using A = typename Tr<P>::acc;
     using In = typename PairIn<P>::T;
@@ -1441,21 +1557,22 @@ k_dslash_eo_pair(Work w, Fld out, Fld in, Fld cen, Fld aux, const double* __rest
     const int lane = threadIdx.x;
     const int r = lane & (w.nr - 1);
     int q = lane >> w.lognr;
-    const int xh = q % Lxh;
+    int xh = q % Lxh;
     q /= Lxh;
-    const int iy = q % TY, iz = q / TY;
+    int iy = q % TY, iz = q / TY;
     const bool valid = iz < TZ;  // lanes beyond the tile only join the barriers
-    const int y = (jt % nty) * TY + iy, z = (jt / nty) * TZ + iz;
+    const int y0 = (jt % nty) * TY, z0 = (jt / nty) * TZ;
+    int y = y0 + iy, z = z0 + iz;
     const int sys = bd.sys0 + r;
     const bool act = valid && mask_ok(mask, st, sys);
     const int vxyzh = Lxh * Ly * Lz;          // field sites of one t-slice
-    const int cb0 = xh + Lxh * (y + Ly * z);  // field index at t = 0
+    int cb0 = xh + Lxh * (y + Ly * z);  // field index at t = 0
     const int ls_y = w.nr * Lxh, ls_z = ls_y * TY;
     const int sy = Lx, sz = Lx * Ly, stt = sz * Lz;
     // x neighbour across the pair boundary: pair xh - 1 when the output column
     // is even, xh + 1 when it is odd (periodic in x; the tile spans all of x)
-    const int lxm = xh == 0 ? lane + (Lxh - 1) * w.nr : lane - w.nr;
-    const int lxp = xh == Lxh - 1 ? lane - (Lxh - 1) * w.nr : lane + w.nr;
+    auto lxm = [&]() { return xh == 0 ? lane + (Lxh - 1) * w.nr : lane - w.nr; };
+    auto lxp = [&]() { return xh == Lxh - 1 ? lane - (Lxh - 1) * w.nr : lane + w.nr; };
 
     double acc[ND];
 #pragma unroll
@@ -1467,7 +1584,7 @@ k_dslash_eo_pair(Work w, Fld out, Fld in, Fld cen, Fld aux, const double* __rest
     if (valid) {
         {
             In e;
-            in_load<P>(ib, inn, gs, ((size_t)(cb0 + t0 * vxyzh) << w.lognr) + r, e);
+            in_load<P, true>(ib, inn, gs, ((size_t)(cb0 + t0 * vxyzh) << w.lognr) + r, e);
             in_put<P>(shb, w.wg, lane, e);
         }
         // backward-t term of the first output: its column at t0 - 1 is this
@@ -1475,7 +1592,7 @@ k_dslash_eo_pair(Work w, Fld out, Fld in, Fld cen, Fld aux, const double* __rest
         const int tb = t0 == 0 ? Lt - 1 : t0 - 1;
         const int xo0 = 2 * xh + ((y + z + t0 + par_out) & 1);
         In v;
-        in_load<P>(ib, inn, gs, ((size_t)(cb0 + tb * vxyzh) << w.lognr) + r, v);
+        in_load<P, true>(ib, inn, gs, ((size_t)(cb0 + tb * vxyzh) << w.lognr) + r, v);
         half_bwd<P, Q, PtP>(ld, 3, xo0 + sy * y + sz * z + stt * tb, v, bw, bws);
         if (t0 == 0 && ld.tsign < 0) bws = -bws;
     }
@@ -1484,46 +1601,95 @@ k_dslash_eo_pair(Work w, Fld out, Fld in, Fld cen, Fld aux, const double* __rest
     for (int t = t0; t < t1; ++t) {
         const char* const sh = shb + (NBUF == 2 ? ((t - t0) & 1) : 0) * LB * w.wg;   // slice t
         char* const shn = shb + (NBUF == 2 ? ((t - t0 + 1) & 1) : 0) * LB * w.wg;    // slice t + 1
+        // opaque here, so that what follows from them (face flags, wrapped
+        // neighbours, LDS and memory offsets) is computed again in every slice:
+        // hoisted out of the loop it took some 30 registers
+        asm volatile("" : "+v"(xh), "+v"(iy), "+v"(iz));
+        y = y0 + iy;
+        z = z0 + iz;
+        cb0 = xh + Lxh * (y + Ly * z);
         const bool wrap = t == Lt - 1;
         const int cb = cb0 + t * vxyzh;
-        In nxt;
+        const int par = (y + z + t + par_out) & 1;  // output column 2 xh + par
+        const int so = 2 * xh + par + sy * y + sz * z + stt * t;
+        const size_t slot = ((size_t)cb << w.lognr) + r;
+        A o[24];
         if (valid) {
-            const int par = (y + z + t + par_out) & 1;  // output column 2 xh + par
-            const int so = 2 * xh + par + sy * y + sz * z + stt * t;
-            const size_t slot = ((size_t)cb << w.lognr) + r;
-            A o[24];
 #pragma unroll
             for (int k = 0; k < 24; ++k) o[k] = A(0);
             PtP::accum(o, bw, A(-0.5) * bws);
-            {  // x: one neighbour is the pair's own input site, the other the next pair's;
-               // the own site also gives the next output's backward-t term
-                In e, l, v;
-                in_get<P>(sh, w.wg, lane, e);
-                half_bwd<P, Q, PtP>(ld, 3, so ^ 1, e, bw, bws);
-                in_get<P>(sh, w.wg, par ? lxp : lxm, l);
-                in_sel<P>(par, l, e, v);
-                hop_fwd<P, Q, PxM>(ld, 0, so, v, o, A(-0.5));
-                in_sel<P>(par, e, l, v);
+            if constexpr (P == P64) {
+                const double2* const sd = reinterpret_cast<const double2*>(sh);
+                auto lds_spin = [&](int nl) {
+                    return [=](int k, double v[6]) {
+#pragma unroll
+                        for (int c = 0; c < 3; ++c) {
+                            const double2 a = sd[(3 * k + c) * w.wg + nl];
+                            v[2 * c] = a.x;
+                            v[2 * c + 1] = a.y;
+                        }
+                    };
+                };
                 const int xo = 2 * xh + par;
-                hop_bwd<P, Q, PxP>(ld, 0, xo == 0 ? so + Lx - 1 : so - 1, v, o, A(-0.5));
+                hop64<Q, true, PxM>(ld, 0, so, lds_spin(par ? lxp() : lane), o, -0.5);
+                            hop64<Q, false, PxP>(ld, 0, xo == 0 ? so + Lx - 1 : so - 1, lds_spin(par ? lane : lxm()), o, -0.5);
+                            pair_hop64<Q, 1, PyM, PyP>(ld, ib, gs, sd, w.wg, lane, iy, TY, Ly, ls_y, y, cb, Lxh, so, sy, r,
+                                           w.lognr, o);
+                            pair_hop64<Q, 2, PzM, PzP>(ld, ib, gs, sd, w.wg, lane, iz, TZ, Lz, ls_z, z, cb, Lxh * Ly, so, sz, r,
+                                           w.lognr, o);
+                __builtin_amdgcn_sched_barrier(0);
+                {
+                    double u[18];
+                    link<P64, Q, double>(ld, 3, so ^ 1, u);
+                    hop_half64<Q, 0, false, PtP>(u, lds_spin(lane), bw);
+                    hop_half64<Q, 1, false, PtP>(u, lds_spin(lane), bw + 6);
+                    bws = 1.0;
+                }
+            } else {
+                {  // x: one neighbour is the pair's own input site, the other the next pair's;
+                   // the own site also gives the next output's backward-t term
+                    In e, l, v;
+                    in_get<P>(sh, w.wg, lane, e);
+                    half_bwd<P, Q, PtP>(ld, 3, so ^ 1, e, bw, bws);
+                    in_get<P>(sh, w.wg, par ? lxp() : lxm(), l);
+                    in_sel<P>(par, l, e, v);
+                    hop_fwd<P, Q, PxM>(ld, 0, so, v, o, A(-0.5));
+                    in_sel<P>(par, e, l, v);
+                    const int xo = 2 * xh + par;
+                    hop_bwd<P, Q, PxP>(ld, 0, xo == 0 ? so + Lx - 1 : so - 1, v, o, A(-0.5));
+                }
+                // scheduling barriers keep each axis's loads in its own phase: hoisted
+                // together they overflow the register file
+                __builtin_amdgcn_sched_barrier(0);
+                pair_hop<P, Q, 1, PyM, PyP>(ld, ib, inn, gs, sh, w.wg, lane, iy, TY, Ly, ls_y, y, cb, Lxh, so, sy, r,
+                                            w.lognr, o);
+                __builtin_amdgcn_sched_barrier(0);
+                pair_hop<P, Q, 2, PzM, PzP>(ld, ib, inn, gs, sh, w.wg, lane, iz, TZ, Lz, ls_z, z, cb, Lxh * Ly, so, sz,
+                                            r, w.lognr, o);
             }
-            // scheduling barriers keep each axis's loads in its own phase: hoisted
-            // together they overflow the register file
-            __builtin_amdgcn_sched_barrier(0);
-            pair_hop<P, Q, 1, PyM, PyP>(ld, ib, inn, gs, sh, w.wg, lane, iy, TY, Ly, ls_y, y, cb, Lxh, so, sy, r,
-                                        w.lognr, o);
-            __builtin_amdgcn_sched_barrier(0);
-            pair_hop<P, Q, 2, PzM, PzP>(ld, ib, inn, gs, sh, w.wg, lane, iz, TZ, Lz, ls_z, z, cb, Lxh * Ly, so, sz,
-                                        r, w.lognr, o);
-            __builtin_amdgcn_sched_barrier(0);
+        }
+        // one buffer: every read of slice t ends before slice t + 1 is written
+        if constexpr (NBUF == 1) __syncthreads();
+        else __builtin_amdgcn_sched_barrier(0);
+        if (valid) {
             {  // t: forward hop from the pair's input site at t + 1 (the next slice's LDS entry)
-                in_load<P>(ib, inn, gs, ((size_t)(wrap ? cb0 : cb + vxyzh) << w.lognr) + r, nxt);
-                hop_fwd<P, Q, PtM>(ld, 3, so, nxt, o, (wrap && ld.tsign < 0) ? A(0.5) : A(-0.5));
+                const size_t fslot = ((size_t)(wrap ? cb0 : cb + vxyzh) << w.lognr) + r;
+                const A cf = (wrap && ld.tsign < 0) ? A(0.5) : A(-0.5);
+                In nxt;
+                in_load<P, true>(ib, inn, gs, fslot, nxt);
+                in_put<P>(shn, w.wg, lane, nxt);
+                if constexpr (P == P64) {
+                    hop64<Q, true, PtM>(ld, 3, so, [&](int k, double v[6]) {
+#pragma unroll
+                        for (int c = 0; c < 6; ++c) v[c] = nxt.v[6 * k + c];
+                    }, o, cf);
+                } else {
+                    hop_fwd<P, Q, PtM>(ld, 3, so, nxt, o, cf);
+                }
             }
-            if (NBUF == 2) in_put<P>(shn, w.wg, lane, nxt);
             A cv[24];
             if constexpr (MODE != D_HOP) {
-                load_sp<P, A>(cen.v + (size_t)bd.slot_off * G, cen.n ? cen.n + bd.slot_off : nullptr, gs, slot, cv);
+                load_sp<P, A, false, true>(cen.v + (size_t)bd.slot_off * G, cen.n ? cen.n + bd.slot_off : nullptr, gs, slot, cv);
                 const A a = (A)diag[sys];
                 if constexpr (CLV) {
                     clv_schur<P, A>(ld, (size_t)cb, a, cv, o);
@@ -1537,11 +1703,11 @@ k_dslash_eo_pair(Work w, Fld out, Fld in, Fld cen, Fld aux, const double* __rest
             }
             if constexpr (MODE == D_RESID) {
                 A bv[24];
-                load_sp<P, A>(aux.v + (size_t)bd.slot_off * G, nullptr, gs, slot, bv);
+                load_sp<P, A, false, true>(aux.v + (size_t)bd.slot_off * G, nullptr, gs, slot, bv);
 #pragma unroll
                 for (int k = 0; k < 24; ++k) o[k] = bv[k] - o[k];
             }
-            store_sp<P, A, true>(ob, on, gs, slot, o);
+            store_sp<P, A, true, true>(ob, on, gs, slot, o);
             if (act) {
                 if constexpr (MODE == D_RHAT) {
                     rhat_code_dots<1, A>(rc[bd.slot_off + slot], o, o, acc, acc);
@@ -1552,10 +1718,6 @@ k_dslash_eo_pair(Work w, Fld out, Fld in, Fld cen, Fld aux, const double* __rest
                     for (int k = 0; k < 24; ++k) acc[0] += (double)o[k] * (double)o[k];
                 }
             }
-        }
-        if (NBUF == 1) {  // one buffer: every read of slice t ends before slice t + 1 is written
-            __syncthreads();
-            if (valid) in_put<P>(shn, w.wg, lane, nxt);
         }
         __syncthreads();
     }
