@@ -473,13 +473,14 @@ struct Plan {
     std::vector<int> wg_start;        // nblk + 1  (tile mapping: vector kernels)
     std::vector<int> wg_start_d;      // nblk + 1  (t-column mapping: stencil)
     int tc = 1;                       // t-slices per stencil workgroup
-    // one-parity plans: the t-streaming mapping of the FP64 source and
-    // reconstruction kernels (the stencil mapping itself when ilp != 2)
+    // one-parity plans: the t-streaming mapping (the stencil mapping itself when
+    // ilp is 0)
     std::vector<int> wg_start_s;
     int tc_s = 1;
     std::vector<std::array<int, 2>> ptile;  // x-pair stencil (ilp 2): TY, TZ per lattice
     std::vector<int> lat_V;           // per lattice
     long long total_slots = 0;
+    long long full_slots = 0;         // one-parity plans: most slots of a block's full-layout field
     // device tables
     DevBuf d_blocks, d_wg_start, d_wg_start_d, d_blk_on;
     DevBuf d_lats[4];
@@ -523,9 +524,12 @@ struct Plan {
         return w;
     }
 
-    // one-parity plans: the t-streaming mapping (FP64 source and reconstruction)
-    Work work_stream(int P) const {
-        Work w = work(P, false, true);
+    // one-parity plans: the mapping of the FP64 source and reconstruction, x-pairs
+    // where the plan has them (and a block's full-layout slots fit the 32-bit
+    // offsets of that stencil), else streaming over t
+    Work work_full() const {
+        Work w = work(P64, false, true);
+        if (ilp == 2 && full_slots <= (1ll << 28)) return w;
         if (eo && ilp >= 2) {
             w.wg_start = d_wg_start_s.as<int>();
             w.total_wg = wg_start_s.back();
@@ -716,7 +720,11 @@ void plan_host(Plan* pl, const std::vector<BlockDesc>& blocks, const std::vector
             lanes += (long long)(c->V / c->dims[3] / 2) * nr;
         }
         long long slots = 0;
-        for (int b = 0; b < nblk; ++b) slots += (long long)(lats[blocks[b].lat]->V >> 1) * nr;
+        for (int b = 0; b < nblk; ++b) {
+            const long long n = (long long)lats[blocks[b].lat]->V * nr;
+            slots += n >> 1;
+            pl->full_slots = std::max(pl->full_slots, n);
+        }
         if (slots <= FS_AXIS_MAX_SLOTS) pl->ilp = 3;
         else if (lanes < FS_PAIR_MIN_LANES || !pair_tiles(nr, wg, lats, pl->ptile)) pl->ilp = 0;
     }
@@ -1194,8 +1202,8 @@ struct BatchSolver {
 
     void run() {
         if (o.eo) {  // Schur source and the full |b|^2 the tolerance refers to
-            // streaming mapping over t; the finish reads that mapping's rows
-            const Work wp = pl.work_stream(P64);
+            // the finish reads the rows of this mapping
+            const Work wp = pl.work_full();
             if (clv) {  // sb_ = b_e - D_eo (C_o + a)^-1 b_o
                 launch_clover_bo_inv(pl.work(P64, false), full.d_blocks.as<BlockDesc>(), b.f(), tmp64.f(), cl64, s);
                 launch_eo_prep_clv(wp, full.d_blocks.as<BlockDesc>(), b.f(), tmp64.f(), sb_.f(),
@@ -1286,10 +1294,10 @@ struct BatchSolver {
         }
         drop_graph();
         if (o.eo && clv)
-            launch_eo_post_clv(pl.work_stream(P64), full.d_blocks.as<BlockDesc>(), b.f(), sx_.f(), xhi.f(),
+            launch_eo_post_clv(pl.work_full(), full.d_blocks.as<BlockDesc>(), b.f(), sx_.f(), xhi.f(),
                                d_diag.as<double>(), cl64, s);
         else if (o.eo)
-            launch_eo_post(pl.work_stream(P64), full.d_blocks.as<BlockDesc>(), b.f(), sx_.f(), xhi.f(),
+            launch_eo_post(pl.work_full(), full.d_blocks.as<BlockDesc>(), b.f(), sx_.f(), xhi.f(),
                            d_diag.as<double>(), s);
         HC(hipMemcpyAsync(st_host.data(), d_st.p, sizeof(SysState) * pl.nsys, hipMemcpyDeviceToHost, s));
         HC(hipStreamSynchronize(s));

@@ -450,24 +450,12 @@ void launch_dslash_eo_clv(int prec, int mode, const Work& w, Fld out, Fld in, Fl
 
 void launch_eo_prep_clv(const Work& wh, const BlockDesc* fblocks, Fld bfull, Fld bo_inv, Fld bh, const double* diag,
                         double* part, hipStream_t s) {
-    const size_t lds = lds_cap(wh.wg, wh.occ);
-    if (wh.nr >= 4)
-        hipLaunchKernelGGL((k_dslash_eo_t<P64, D_PREP, 1, 1>), dim3(grid_of(wh)), dim3(wh.wg), lds, s, wh, bh, bo_inv,
-                           Fld(), bfull, diag, nullptr, (int)M_ALL, part, nullptr, 0, fblocks, Clv());
-    else
-        hipLaunchKernelGGL((k_dslash_eo_t<P64, D_PREP, 0, 1>), dim3(grid_of(wh)), dim3(wh.wg), lds, s, wh, bh, bo_inv,
-                           Fld(), bfull, diag, nullptr, (int)M_ALL, part, nullptr, 0, fblocks, Clv());
+    launch_eo_full<D_PREP, 1>(wh, fblocks, bh, bo_inv, bfull, diag, part, 0, Clv(), s);
 }
 
 void launch_eo_post_clv(const Work& wh, const BlockDesc* fblocks, Fld bfull, Fld xh, Fld xfull, const double* diag,
                         const Clv& cl64, hipStream_t s) {
-    const size_t lds = lds_cap(wh.wg, wh.occ);
-    if (wh.nr >= 4)
-        hipLaunchKernelGGL((k_dslash_eo_t<P64, D_POST, 1, 1>), dim3(grid_of(wh)), dim3(wh.wg), lds, s, wh, xfull, xh,
-                           Fld(), bfull, diag, nullptr, (int)M_ALL, nullptr, nullptr, 1, fblocks, cl64);
-    else
-        hipLaunchKernelGGL((k_dslash_eo_t<P64, D_POST, 0, 1>), dim3(grid_of(wh)), dim3(wh.wg), lds, s, wh, xfull, xh,
-                           Fld(), bfull, diag, nullptr, (int)M_ALL, nullptr, nullptr, 1, fblocks, cl64);
+    launch_eo_full<D_POST, 1>(wh, fblocks, xfull, xh, bfull, diag, nullptr, 1, cl64, s);
 }
 
 }  // namespace fs

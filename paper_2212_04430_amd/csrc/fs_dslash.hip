@@ -108,14 +108,8 @@ void launch_dslash_eo(int prec, int mode, const Work& w, Fld out, Fld in, Fld ce
 
 void launch_eo_prep(const Work& wh, const BlockDesc* fblocks, Fld bfull, Fld bh, const double* diag, double* part,
                     hipStream_t s) {
-    if (wh.tc > 0) {  // stencil mapping: stream over t
-        const size_t lds = lds_cap(wh.wg, wh.occ);
-        if (wh.nr >= 4)
-            hipLaunchKernelGGL((k_dslash_eo_t<P64, D_PREP, 1>), dim3(grid_of(wh)), dim3(wh.wg), lds, s, wh, bh, bfull,
-                               Fld(), Fld(), diag, nullptr, (int)M_ALL, part, nullptr, 0, fblocks, Clv());
-        else
-            hipLaunchKernelGGL((k_dslash_eo_t<P64, D_PREP, 0>), dim3(grid_of(wh)), dim3(wh.wg), lds, s, wh, bh, bfull,
-                               Fld(), Fld(), diag, nullptr, (int)M_ALL, part, nullptr, 0, fblocks, Clv());
+    if (wh.tc > 0) {
+        launch_eo_full<D_PREP, 0>(wh, fblocks, bh, bfull, Fld(), diag, part, 0, Clv(), s);
         return;
     }
     if (wh.nr >= 4)
@@ -126,14 +120,8 @@ void launch_eo_prep(const Work& wh, const BlockDesc* fblocks, Fld bfull, Fld bh,
 
 void launch_eo_post(const Work& wh, const BlockDesc* fblocks, Fld bfull, Fld xh, Fld xfull, const double* diag,
                     hipStream_t s) {
-    if (wh.tc > 0) {  // stencil mapping: stream over t
-        const size_t lds = lds_cap(wh.wg, wh.occ);
-        if (wh.nr >= 4)
-            hipLaunchKernelGGL((k_dslash_eo_t<P64, D_POST, 1>), dim3(grid_of(wh)), dim3(wh.wg), lds, s, wh, xfull, xh,
-                               Fld(), bfull, diag, nullptr, (int)M_ALL, nullptr, nullptr, 1, fblocks, Clv());
-        else
-            hipLaunchKernelGGL((k_dslash_eo_t<P64, D_POST, 0>), dim3(grid_of(wh)), dim3(wh.wg), lds, s, wh, xfull, xh,
-                               Fld(), bfull, diag, nullptr, (int)M_ALL, nullptr, nullptr, 1, fblocks, Clv());
+    if (wh.tc > 0) {
+        launch_eo_full<D_POST, 0>(wh, fblocks, xfull, xh, bfull, diag, nullptr, 1, Clv(), s);
         return;
     }
     if (wh.nr >= 4)

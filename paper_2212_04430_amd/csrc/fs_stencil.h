@@ -1413,7 +1413,10 @@ __global__ void __launch_bounds__(256) k_dslash_eo_axis(Work w, Fld out, Fld in,
 // launches fit all the same (FP32 D_TS 1.04 ms scheduled for three waves, 0.97 for one).
 // 432 systems on 16^3x32: FP32 hop 1.68 -> 1.61 ms, FP64 hop 5.39 -> 3.78 (the
 // smallest possible traffic at copy rate: 2.9); averages over a solve: FP32 D_RHAT
-// 1.01 -> 0.94 ms, D_TS 1.15 -> 0.97, FP64 residual 0.87 -> 0.75.
+// 1.01 -> 0.94 ms, D_TS 1.15 -> 0.97, FP64 residual 0.87 -> 0.75.  The FP64 source
+// (D_PREP) and reconstruction (D_POST) of that batch, streaming over t and here:
+// 9.8 and 7.0 ms, 9.9 and 7.4; they use half of each line of a full-layout field at
+// a time.
 //
 // One neighbour of the x-pair stencil: from LDS when it is inside the tile,
 // else from memory; every lane issues the memory load (interior lanes load
@@ -1498,15 +1501,17 @@ __device__ __forceinline__ void hop64(const LatDesc& ld, int mu, int lsite, F&& 
     }
     __builtin_amdgcn_sched_barrier(0);
 }
-template <int Q, int MU, typename PF, typename PB>
+// FULL: the input is a full-layout field; bit = the input site of a pair's two.
+template <int Q, bool FULL, int MU, typename PF, typename PB>
 __device__ __forceinline__ void pair_hop64(const LatDesc& ld, const uint4* __restrict__ ib, size_t gs,
                                            const double2* sh, int wg, int lane, int i, int T, int Lm, int ls, int c,
-                                           int cb, int cstride, int so, int sstride, int r, int lognr, double o[24]) {
+                                           int cb, int bit, int cstride, int so, int sstride, int r, int lognr,
+                                           double o[24]) {
     const bool whole = T == Lm;  // the tile spans the axis: wrap-around inside it
     {
         const int cbf = (c == Lm - 1) ? cb - (Lm - 1) * cstride : cb + cstride;
         const bool inside = whole || i < T - 1;
-        const size_t gslot = inside ? (size_t)0 : ((size_t)cbf << lognr) + r;
+        const size_t gslot = inside ? (size_t)0 : ((size_t)(FULL ? 2 * cbf + bit : cbf) << lognr) + r;
         const int nl = (i < T - 1) ? lane + ls : lane - (T - 1) * ls;
         hop64<Q, true, PF>(ld, MU, so, [&](int k, double v[6]) {
             pair_spin64(inside, ib, gs, gslot, sh, wg, nl, k, v);
@@ -1516,7 +1521,7 @@ __device__ __forceinline__ void pair_hop64(const LatDesc& ld, const uint4* __res
         const int cbb = (c == 0) ? cb + (Lm - 1) * cstride : cb - cstride;
         const int sb = (c == 0) ? so + (Lm - 1) * sstride : so - sstride;
         const bool inside = whole || i > 0;
-        const size_t gslot = inside ? (size_t)0 : ((size_t)cbb << lognr) + r;
+        const size_t gslot = inside ? (size_t)0 : ((size_t)(FULL ? 2 * cbb + bit : cbb) << lognr) + r;
         const int nl = (i > 0) ? lane - ls : lane + (T - 1) * ls;
         hop64<Q, false, PB>(ld, MU, sb, [&](int k, double v[6]) {
             pair_spin64(inside, ib, gs, gslot, sh, wg, nl, k, v);
@@ -1528,8 +1533,12 @@ __global__ void __launch_bounds__(256) k_dslash_eo_pair(Work w, Fld out, Fld in,
                                                         const double* __restrict__ diag,
                                                         const SysState* __restrict__ st, int mask,
                                                         double* __restrict__ part, const uint32_t* __restrict__ rc,
-                                                        int par_out, Clv cl) {
+                                                        int par_out, const BlockDesc* __restrict__ fblocks, Clv cl) {
     static_assert(!CLV || P == P64 || P == P32, "the clover term is kept in FP64 and FP32");
+    // D_PREP and D_POST as in k_dslash_eo_t
+    constexpr bool FULL_IN = MODE == D_PREP && !CLV;
+    constexpr bool FULL_OUT = MODE == D_POST;
+    static_assert(!(MODE == D_PREP || FULL_OUT) || P == P64, "the even-odd source and reconstruction are FP64");
     using A = typename Tr<P>::acc;
     using In = typename PairIn<P>::T;
     constexpr int G = Tr<P>::G;
@@ -1543,9 +1552,12 @@ __global__ void __launch_bounds__(256) k_dslash_eo_pair(Work w, Fld out, Fld in,
     const LatDesc ld = w.lats[bd.lat];
     const int wgb = wg_id - w.wg_start[b];
     const size_t gs = (size_t)ld.Vf << w.lognr;
-    const uint4* ib = in.v + (size_t)bd.slot_off * G;
+    const size_t gsf = (size_t)ld.V << w.lognr;  // full-layout fields
+    const size_t gsi = FULL_IN ? gsf : gs;       // the hop input
+    const long long foff = (MODE == D_PREP || FULL_OUT) ? fblocks[b].slot_off : 0;
+    const uint4* ib = in.v + (size_t)(FULL_IN ? foff : bd.slot_off) * G;
     const float* inn = in.n ? in.n + bd.slot_off : nullptr;
-    uint4* ob = out.v + (size_t)bd.slot_off * G;
+    uint4* ob = out.v + (size_t)(FULL_OUT ? foff : bd.slot_off) * G;
     float* on = out.n ? out.n + bd.slot_off : nullptr;
     const int Lx = ld.L[0], Ly = ld.L[1], Lz = ld.L[2], Lt = ld.L[3];
     const int Lxh = Lx >> 1;
@@ -1574,6 +1586,8 @@ __global__ void __launch_bounds__(256) k_dslash_eo_pair(Work w, Fld out, Fld in,
     auto lxm = [&]() { return xh == 0 ? lane + (Lxh - 1) * w.nr : lane - w.nr; };
     auto lxp = [&]() { return xh == Lxh - 1 ? lane - (Lxh - 1) * w.nr : lane + w.nr; };
 
+    // slot of the input site of field index c; bit: which of the pair's two it is
+    auto islot = [&](int c, int bit) { return ((size_t)(FULL_IN ? 2 * c + bit : c) << w.lognr) + r; };
     double acc[ND];
 #pragma unroll
     for (int k = 0; k < ND; ++k) acc[k] = 0.0;
@@ -1584,7 +1598,7 @@ __global__ void __launch_bounds__(256) k_dslash_eo_pair(Work w, Fld out, Fld in,
     if (valid) {
         {
             In e;
-            in_load<P, true>(ib, inn, gs, ((size_t)(cb0 + t0 * vxyzh) << w.lognr) + r, e);
+            in_load<P, true>(ib, inn, gsi, islot(cb0 + t0 * vxyzh, (y + z + t0 + par_out + 1) & 1), e);
             in_put<P>(shb, w.wg, lane, e);
         }
         // backward-t term of the first output: its column at t0 - 1 is this
@@ -1592,7 +1606,7 @@ __global__ void __launch_bounds__(256) k_dslash_eo_pair(Work w, Fld out, Fld in,
         const int tb = t0 == 0 ? Lt - 1 : t0 - 1;
         const int xo0 = 2 * xh + ((y + z + t0 + par_out) & 1);
         In v;
-        in_load<P, true>(ib, inn, gs, ((size_t)(cb0 + tb * vxyzh) << w.lognr) + r, v);
+        in_load<P, true>(ib, inn, gsi, islot(cb0 + tb * vxyzh, (y + z + t0 + par_out) & 1), v);
         half_bwd<P, Q, PtP>(ld, 3, xo0 + sy * y + sz * z + stt * tb, v, bw, bws);
         if (t0 == 0 && ld.tsign < 0) bws = -bws;
     }
@@ -1633,16 +1647,32 @@ __global__ void __launch_bounds__(256) k_dslash_eo_pair(Work w, Fld out, Fld in,
                 const int xo = 2 * xh + par;
                 hop64<Q, true, PxM>(ld, 0, so, lds_spin(par ? lxp() : lane), o, -0.5);
                             hop64<Q, false, PxP>(ld, 0, xo == 0 ? so + Lx - 1 : so - 1, lds_spin(par ? lane : lxm()), o, -0.5);
-                            pair_hop64<Q, 1, PyM, PyP>(ld, ib, gs, sd, w.wg, lane, iy, TY, Ly, ls_y, y, cb, Lxh, so, sy, r,
-                                           w.lognr, o);
-                            pair_hop64<Q, 2, PzM, PzP>(ld, ib, gs, sd, w.wg, lane, iz, TZ, Lz, ls_z, z, cb, Lxh * Ly, so, sz, r,
-                                           w.lognr, o);
+                            pair_hop64<Q, FULL_IN, 1, PyM, PyP>(ld, ib, gsi, sd, w.wg, lane, iy, TY, Ly, ls_y, y, cb, par, Lxh, so, sy,
+                                                    r, w.lognr, o);
+                            pair_hop64<Q, FULL_IN, 2, PzM, PzP>(ld, ib, gsi, sd, w.wg, lane, iz, TZ, Lz, ls_z, z, cb, par, Lxh * Ly, so,
+                                                    sz, r, w.lognr, o);
                 __builtin_amdgcn_sched_barrier(0);
                 {
                     double u[18];
                     link<P64, Q, double>(ld, 3, so ^ 1, u);
-                    hop_half64<Q, 0, false, PtP>(u, lds_spin(lane), bw);
-                    hop_half64<Q, 1, false, PtP>(u, lds_spin(lane), bw + 6);
+                    // the pair's own input site: D_PREP's b_o, D_POST's x_e
+                    auto own = [&](int k, double v[6]) {
+                        lds_spin(lane)(k, v);
+                        if constexpr (FULL_IN) {
+                            if (act) {
+#pragma unroll
+                                for (int c = 0; c < 6; ++c) acc[0] += v[c] * v[c];
+                            }
+                        }
+                        if constexpr (FULL_OUT) {
+#pragma unroll
+                            for (int c = 0; c < 3; ++c)
+                                st16<true>(atg<true>(ob + (3 * k + c) * gsf, ((size_t)(so ^ 1) << w.lognr) + r),
+                                           pack_d(v[2 * c], v[2 * c + 1]));
+                        }
+                    };
+                    hop_half64<Q, 0, false, PtP>(u, own, bw);
+                    hop_half64<Q, 1, false, PtP>(u, own, bw + 6);
                     bws = 1.0;
                 }
             } else {
@@ -1673,10 +1703,10 @@ __global__ void __launch_bounds__(256) k_dslash_eo_pair(Work w, Fld out, Fld in,
         else __builtin_amdgcn_sched_barrier(0);
         if (valid) {
             {  // t: forward hop from the pair's input site at t + 1 (the next slice's LDS entry)
-                const size_t fslot = ((size_t)(wrap ? cb0 : cb + vxyzh) << w.lognr) + r;
+                const size_t fslot = islot(wrap ? cb0 : cb + vxyzh, par);
                 const A cf = (wrap && ld.tsign < 0) ? A(0.5) : A(-0.5);
                 In nxt;
-                in_load<P, true>(ib, inn, gs, fslot, nxt);
+                in_load<P, true>(ib, inn, gsi, fslot, nxt);
                 in_put<P>(shn, w.wg, lane, nxt);
                 if constexpr (P == P64) {
                     hop64<Q, true, PtM>(ld, 3, so, [&](int k, double v[6]) {
@@ -1688,7 +1718,30 @@ __global__ void __launch_bounds__(256) k_dslash_eo_pair(Work w, Fld out, Fld in,
                 }
             }
             A cv[24];
-            if constexpr (MODE != D_HOP) {
+            if constexpr (MODE == D_PREP || FULL_OUT) {
+                // D_PREP: out_e = b_e - D_eo b_o / a and |b_e|^2 + |b_o|^2; D_POST: x_o =
+                // (b_o - D_oe x_e) / a.  The clover term's 1 / a is in the input, or follows.
+                const A ia = CLV ? A(1) : A(1) / (A)diag[sys];
+                const uint4* const bsrc = FULL_IN ? ib : aux.v + (size_t)foff * G;  // the full-layout source
+                load_sp<P, A, false, true>(bsrc, nullptr, gsf, ((size_t)so << w.lognr) + r, cv);
+                if constexpr (MODE == D_PREP) {
+#pragma unroll
+                    for (int k = 0; k < 24; ++k) {
+                        if (act) acc[0] += (double)cv[k] * (double)cv[k];
+                        o[k] = cv[k] - ia * o[k];
+                    }
+                    if constexpr (CLV) {
+                        load_sp<P, A, false, true>(bsrc, nullptr, gsf, ((size_t)(so ^ 1) << w.lognr) + r, cv);
+#pragma unroll
+                        for (int k = 0; k < 24; ++k)
+                            if (act) acc[0] += (double)cv[k] * (double)cv[k];
+                    }
+                } else {
+#pragma unroll
+                    for (int k = 0; k < 24; ++k) o[k] = ia * (cv[k] - o[k]);
+                    if constexpr (CLV) clv_inv<P, A>(cl, ld, sys, (size_t)cb, o);
+                }
+            } else if constexpr (MODE != D_HOP) {
                 load_sp<P, A, false, true>(cen.v + (size_t)bd.slot_off * G, cen.n ? cen.n + bd.slot_off : nullptr, gs, slot, cv);
                 const A a = (A)diag[sys];
                 if constexpr (CLV) {
@@ -1707,7 +1760,8 @@ __global__ void __launch_bounds__(256) k_dslash_eo_pair(Work w, Fld out, Fld in,
 #pragma unroll
                 for (int k = 0; k < 24; ++k) o[k] = bv[k] - o[k];
             }
-            store_sp<P, A, true, true>(ob, on, gs, slot, o);
+            if constexpr (FULL_OUT) store_sp<P, A, true, true>(ob, nullptr, gsf, ((size_t)so << w.lognr) + r, o);
+            else store_sp<P, A, true, true>(ob, on, gs, slot, o);
             if (act) {
                 if constexpr (MODE == D_RHAT) {
                     rhat_code_dots<1, A>(rc[bd.slot_off + slot], o, o, acc, acc);
@@ -1721,7 +1775,8 @@ __global__ void __launch_bounds__(256) k_dslash_eo_pair(Work w, Fld out, Fld in,
         }
         __syncthreads();
     }
-    if constexpr (MODE == D_RHAT || MODE == D_TS || MODE == D_RESID) block_partials<ND, 4>(acc, w.nr, part, wg_id);
+    if constexpr (MODE == D_RHAT || MODE == D_TS || MODE == D_RESID || MODE == D_PREP)
+        block_partials<ND, 4>(acc, w.nr, part, wg_id);
     });
 }
 
@@ -1822,6 +1877,31 @@ static size_t lds_cap(int wg, int waves) {
 template <int P>
 static int qmode(const Work& w) { return w.nr < 4 ? 0 : (P == P32 && w.two_rows) ? 2 : 1; }
 
+// D_PREP and D_POST (FP64): the x-pair or the t-streaming stencil of the mapping w
+template <int MODE, int CLV>
+static void launch_eo_full(const Work& w, const BlockDesc* fblocks, Fld out, Fld in, Fld aux, const double* diag,
+                           double* part, int par_out, const Clv& cl, hipStream_t s) {
+    const size_t cap = lds_cap(w.wg, w.occ);
+    const dim3 grid(grid_of(w)), wg(w.wg);
+    const int mask = (int)M_ALL;
+    if (w.ilp == 2) {
+        const size_t lds = std::max((size_t)tile_nbuf<P64>() * in_lds_bytes<P64>() * w.wg, cap);
+        if (w.nr >= 4)
+            hipLaunchKernelGGL((k_dslash_eo_pair<P64, MODE, 1, CLV>), grid, wg, lds, s, w, out, in, Fld(), aux, diag,
+                               nullptr, mask, part, nullptr, par_out, fblocks, cl);
+        else
+            hipLaunchKernelGGL((k_dslash_eo_pair<P64, MODE, 0, CLV>), grid, wg, lds, s, w, out, in, Fld(), aux, diag,
+                               nullptr, mask, part, nullptr, par_out, fblocks, cl);
+        return;
+    }
+    if (w.nr >= 4)
+        hipLaunchKernelGGL((k_dslash_eo_t<P64, MODE, 1, CLV>), grid, wg, cap, s, w, out, in, Fld(), aux, diag, nullptr,
+                           mask, part, nullptr, par_out, fblocks, cl);
+    else
+        hipLaunchKernelGGL((k_dslash_eo_t<P64, MODE, 0, CLV>), grid, wg, cap, s, w, out, in, Fld(), aux, diag, nullptr,
+                           mask, part, nullptr, par_out, fblocks, cl);
+}
+
 template <int P, int MODE, int CLV = 0>
 static void launch_eo_q(const Work& w, Fld out, Fld in, Fld cen, Fld aux, const double* diag, const SysState* st,
                         int mask, double* part, hipStream_t s, const uint32_t* rc, int par_out,
@@ -1851,15 +1931,18 @@ static void launch_eo_q(const Work& w, Fld out, Fld in, Fld cen, Fld aux, const 
             case 2:
                 if constexpr (P == P32)
                     hipLaunchKernelGGL((k_dslash_eo_pair<P, MODE, 2, CLV>), dim3(grid_of(w)), dim3(w.wg), lds, s, w, out,
-                                       in, cen, aux, diag, st, mask, part, rc, par_out, cl);
+                                       in, cen, aux, diag, st, mask, part, rc, par_out, nullptr,
+                                   cl);
                 break;
             case 1:
                 hipLaunchKernelGGL((k_dslash_eo_pair<P, MODE, 1, CLV>), dim3(grid_of(w)), dim3(w.wg), lds, s, w, out, in,
-                                   cen, aux, diag, st, mask, part, rc, par_out, cl);
+                                   cen, aux, diag, st, mask, part, rc, par_out, nullptr,
+                                   cl);
                 break;
             default:
                 hipLaunchKernelGGL((k_dslash_eo_pair<P, MODE, 0, CLV>), dim3(grid_of(w)), dim3(w.wg), lds, s, w, out, in,
-                                   cen, aux, diag, st, mask, part, rc, par_out, cl);
+                                   cen, aux, diag, st, mask, part, rc, par_out, nullptr,
+                                   cl);
         }
         return;
     }

@@ -66,5 +66,7 @@ def test_at_the_rule(n):
 
 
 @pytest.mark.parametrize("dims", [(16, 16, 12, 12), (16, 16, 16, 8)])
-def test_at_the_pair_rule(dims):
-    _solve(dims, "f32", 4, True, 0.0, 11, sig=(0.0,))  # 18432 and 24576 pairs of columns: streaming, x-pairs
+@pytest.mark.parametrize("storage,csw", [("f32", 0.0), ("f32", 1.1), ("f64", 0.0), ("f64", 1.1)])
+def test_at_the_pair_rule(dims, storage, csw):
+    # 18432 and 24576 pairs of columns: the source, the iteration and the reconstruction streaming, or in x-pairs
+    _solve(dims, storage, 4, not csw, csw, 11, sig=(0.0,))
