@@ -493,8 +493,8 @@ fs_status fs_time_dslash_eo_each(fs_ctx ctx, fs_prec storage, int32_t n_sys, int
  *              slice earlier -- is shared through LDS with the x/y/z neighbours
  *              of a tile of (Lx/2) x TY x TZ pairs; where no tile fits the
  *              work-group or the tiles are too few for the chip, variant 0 runs,
- *              and where all output sites of the batch are fewer than 131072
- *              lanes a form that splits each site's eight hops over four waves.
+ *              and where all output sites of the batch are at most 131072
+ *              (FP64: 49152) a form that splits each site's eight hops over four waves.
  *   occ        cap on resident waves per SIMD, 0..8 (0 = none), -1 = the
  *              variant's default (variant 0: 3 for FP32 rhs block 4, else none;
  *              variant 2: none).

@@ -594,9 +594,14 @@ static bool choose_tile(int sites, const std::vector<fs_ctx_s*>& lats, int tl[3]
 // variant: 4 FP64 systems on 8^3x16 (16384) 6.7 -> 5.4 ms, 24 FP32 systems on
 // 8^2x6x20 (92160) 7.4 -> 6.6 ms; from 262144 on the two are within 2 % of each other
 // (50 systems on 8^3x16 27.1 and 27.7 ms), and the streaming one loads fewer links.
+// FP64 three eighths of that: the solves of two systems on 16^3x32 (131072) 22.7 and
+// 20.8 ms streaming, of six on 12^3x24 (124416) 18.2 and 15.6, of four there (82944)
+// 13.8 either way, of two on 16^4 (65536) 12.2 and 11.0, the 4^4 estimate of 320
+// (40960) 3.5 and 4.0.
 #ifndef FS_AXIS_MAX_SLOTS
 #define FS_AXIS_MAX_SLOTS (256 * 4 * 2 * 64)
 #endif
+static long long axis_max_slots(int P) { return P == P64 ? FS_AXIS_MAX_SLOTS * 3 / 8 : FS_AXIS_MAX_SLOTS; }
 // x-pair stencil: at least this many lanes (pairs of columns times systems),
 // else the t-streaming variant, which splits small batches finer.  Whole solves,
 // streaming and pairs: 24 FP32 systems on 16^3x32 (49152 lanes) 64.9 and 57.4 ms,
@@ -645,7 +650,7 @@ static bool pair_tiles(int nr, int wg, const std::vector<fs_ctx_s*>& lats, std::
 
 // The host side of a plan (no device tables): mappings and workgroup counts.
 void plan_host(Plan* pl, const std::vector<BlockDesc>& blocks, const std::vector<fs_ctx_s*>& lats, int nr, int wg,
-               int ilp, int occ, int eo) {
+               int ilp, int occ, int eo, int P = P32) {
     pl->nr = nr;
     pl->eo = eo;
     pl->ilp = ilp;
@@ -725,7 +730,7 @@ void plan_host(Plan* pl, const std::vector<BlockDesc>& blocks, const std::vector
             slots += n >> 1;
             pl->full_slots = std::max(pl->full_slots, n);
         }
-        if (slots <= FS_AXIS_MAX_SLOTS) pl->ilp = 3;
+        if (slots <= axis_max_slots(P)) pl->ilp = 3;
         else if (lanes < FS_PAIR_MIN_LANES || !pair_tiles(nr, wg, lats, pl->ptile)) pl->ilp = 0;
     }
     if (eo && pl->ilp == 3) {  // a site's hops split over four waves: 64 slots per workgroup
@@ -774,9 +779,10 @@ void plan_host(Plan* pl, const std::vector<BlockDesc>& blocks, const std::vector
 }
 
 std::unique_ptr<Plan> plan_from_blocks(const std::vector<BlockDesc>& blocks, const std::vector<fs_ctx_s*>& lats,
-                                       int nr, int wg, hipStream_t s, int ilp, int occ, int eo = 0) {
+                                       int nr, int wg, hipStream_t s, int ilp, int occ, int eo = 0,
+                                       int P = P32) {
     auto pl = std::make_unique<Plan>();
-    plan_host(pl.get(), blocks, lats, nr, wg, ilp, occ, eo);
+    plan_host(pl.get(), blocks, lats, nr, wg, ilp, occ, eo, P);
     const int nblk = (int)blocks.size();
     const int nb1 = std::max(nblk, 1);
     pl->d_blocks.alloc(sizeof(BlockDesc) * nb1);
@@ -851,7 +857,7 @@ std::unique_ptr<Plan> eo_plan_of(const Plan& full, const std::vector<fs_ctx_s*>&
         bd.slot_off = off;
         off += (long long)(lats[bd.lat]->V / 2) * full.nr;
     }
-    auto pl = plan_from_blocks(blocks, lats, full.nr, full.wg, s, var, std::max(occ, 0), 1);
+    auto pl = plan_from_blocks(blocks, lats, full.nr, full.wg, s, var, std::max(occ, 0), 1, P);
     if (occ < 0) pl->occ = pl->ilp == 2 ? 0 : eo_occ(P, full.nr);  // launch-time only: no table depends on it
     return pl;
 }
@@ -1093,7 +1099,9 @@ struct BatchSolver {
     // without work leave after reading their block's flag.
     // (Clover sampling on 12^3x24, up to 6100 workgroups: 72.5 ms with lists above
     // 2048, 84.2 ms with the same launches whole.)
-    bool lists() const { return cur->max_wg() > 2048; }
+    // FP64 streaming plans keep the list at every size: two systems on 16^3x32, hop 41
+    // us listed and 60 whole.
+    bool lists() const { return cur->max_wg() > 2048 || (o.P == P64 && cur->ilp == 0); }
     // launch over the blocks of list vl, or of the flags it is built from (tile
     // or stencil mapping)
     Work listed(const VList& vl, int P, bool stencil) {
@@ -1183,7 +1191,8 @@ struct BatchSolver {
             if (any) keep.push_back(bd);
         }
         if (keep.empty() || keep.size() == cur->blocks.size()) return false;
-        auto np = plan_from_blocks(keep, lats, pl.nr, pl.wg, s, o.eo ? o.eo_var : pl.ilp, pl.occ, pl.eo);
+        auto np = plan_from_blocks(keep, lats, pl.nr, pl.wg, s, o.eo ? o.eo_var : pl.ilp, pl.occ, pl.eo,
+                                   o.P);
         if (part_need(*np) > part_doubles) {
             part_doubles = part_need(*np);
             d_part.alloc(sizeof(double) * part_doubles);

@@ -2,7 +2,7 @@
 
 Sizes at its edges: fewer slots (sites of one parity times systems per block) than one workgroup of 64, a last
 workgroup that is nearly empty, padded blocks, two-site axes, several blocks with their own first workgroup, and both
-sides of the 131072 slots up to which it runs.  As for the other stencils the returned x is pinned by the true residual,
+sides of the 131072 (FP64: 49152) slots up to which it runs.  As for the other stencils the returned x is pinned by the true residual,
 recomputed by the oracle: at most 1.5 times the tolerance that the solver reports it met.
 """
 
@@ -63,6 +63,11 @@ def test_whole_links():
 @pytest.mark.parametrize("n", [8, 9])
 def test_at_the_rule(n):
     _solve((16, 8, 16, 16), "f32", 4, True, 0.0, n, sig=(0.0,))  # 131072 and 196608 slots
+
+
+@pytest.mark.parametrize("n", [8, 9])
+def test_at_the_rule_f64(n):
+    _solve((16, 8, 8, 12), "f64", 4, True, 0.0, n, sig=(0.0,))  # 49152 and 73728 slots
 
 
 @pytest.mark.parametrize("dims", [(16, 16, 12, 12), (16, 16, 16, 8)])
